@@ -104,7 +104,7 @@ __device__ __forceinline__ void dq_probs(const f32x4 (&s)[2], const f32x4 (&dp)[
         }
 }
 
-template <int D, bool GPROJ, bool WRITE_Z, int NB = 2>
+template <int D, bool GPROJ, bool WRITE_Z, int NB, bool UNEVEN>
 __global__ __launch_bounds__(kThreads * 2 / NB, D == 64 ? GPA_DQ_OCC64 : 2 / NB)
 void bwd_dq_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
@@ -132,10 +132,12 @@ void bwd_dq_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
+    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
+    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head
     const size_t kvoff = sr.kv0 * D;  // its key/value head
@@ -438,7 +440,7 @@ __device__ __forceinline__ void dkdv_probs(const f32x4& s, const f32x4& dp, cons
 // rho_acc, m_acc, all by atomic adds; the key correction is then a second
 // pass (bwd_dk_corr_kernel), so the FP32 dK^acc = t^T Q goes to dKacc
 // unscaled when dKacc is given (else dK = BF16(alpha dK^acc), as in plain).
-template <int D, bool GPROJ, bool FUSED_DQ = false>
+template <int D, bool GPROJ, bool FUSED_DQ, bool UNEVEN>
 __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dkdv_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
@@ -482,10 +484,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     const int Tq = (Nmax + kTile - 1) / kTile;   // query tiles of the longest problem
     const int Tk = (Nkmax + kTile - 1) / kTile;  // key tiles of the longest problem
     int bh, tile;
-    map_block(blockIdx.x, BH, Tk, false, &bh, &tile);
+    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, Tk, &bh, &tile);
+    else map_block(blockIdx.x, BH, Tk, false, &bh, &tile);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if (tile * kTile >= Nk) return;  // a shorter sequence has no such tile
+    if constexpr (UNEVEN) tile = packed_tile(tile, Tk, (Nk + kTile - 1) / kTile, false);
+    if ((UNEVEN && tile < 0) || tile * kTile >= Nk) return;  // a shorter sequence has no such tile
     const int T = (N + kTile - 1) / kTile;
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head: Q, dO, z
@@ -816,6 +820,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     // A key tile that no query sees (qt0 >= T) takes no step and stores zeros.
     if (qt0 < T) step(masked, qt0, B0, B2);
     if (qt0 + 1 < T) step(masked, qt0 + 1, B1, B0);
+    // Pin where the loop's code starts: 16 bytes into a 32-byte window.  The
+    // same instructions run 88 us there and 92 (0 bytes) to 95 us (24 bytes) at
+    // h16_n4096_d64 gproj; without this, any edit before the loop moves it.
+    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int qt = qt0 + 2; qt < T; qt += 3) {
         step(plain, qt, B2, B1);
         if (qt + 1 < T) step(plain, qt + 1, B0, B2);
@@ -1262,7 +1270,7 @@ hipError_t launch_bwd_fused(const uint16_t* Q, const uint16_t* K, const uint16_t
     dim3 grid((unsigned)(s.BH * Tk)), block(kThreads);
     float* dKacc = mode == 2 ? a.dKacc : nullptr;
 #define GPA_FUSED(DD, GP)                                                                    \
-    launch_kernel(bwd_dkdv_kernel<DD, GP, true>, grid, block, st, Q, K, V, dO, TS, nullptr,  \
+    launch_kernel(bwd_dkdv_kernel<DD, GP, true, false>, grid, block, st, Q, K, V, dO, TS, nullptr,  \
                   dK, dV, nullptr, nullptr, s.BH, s.N, s.causal, s.scale, 1, nullptr, s.BH, 0, \
                   nullptr, 0, s.N, a.A, a.B, a.rho, a.m, dKacc)
     if (s.d == 64) {
@@ -1317,10 +1325,12 @@ hipError_t launch_bwd_dq(const uint16_t* Q, const uint16_t* K, const uint16_t* V
     const int T = (s.N + kTile - 1) / kTile;
     const int Nk = s.Nk > 0 ? s.Nk : s.N;
     dim3 grid((unsigned)(s.BH * T)), block(kThreads);
+    const bool uneven = uneven_pack(s, s.total, s.N);
 #define GPA_DQ(DD, GP, WZ, NB)                                                                \
-    launch_kernel(bwd_dq_kernel<DD, GP, WZ, NB>, grid, block, st, Q, K, V, O, dO, LSE, Drow, TS, \
-                  dQ, rho, msum, lambda, Z, s.BH, s.N, s.causal, s.scale, s.G, s.cu, s.Hq,    \
-                  s.total, s.cu_k, s.total_k, Nk)
+    launch_kernel(uneven ? bwd_dq_kernel<DD, GP, WZ, NB, true>                                \
+                         : bwd_dq_kernel<DD, GP, WZ, NB, false>,                              \
+                  grid, block, st, Q, K, V, O, dO, LSE, Drow, TS, dQ, rho, msum, lambda, Z,   \
+                  s.BH, s.N, s.causal, s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, Nk)
     if (s.d == 64) {
         if (mode == 2) GPA_DQ(64, true, true, 2);
         else if (mode == 1) GPA_DQ(64, true, false, 2);
@@ -1345,10 +1355,13 @@ hipError_t launch_bwd_dkdv(const uint16_t* Q, const uint16_t* K, const uint16_t*
     const int Tk = (Nk + kTile - 1) / kTile;
     dim3 grid((unsigned)(s.BH * Tk)), block(kThreads);
     const bool gp = mode == 2;
+    const bool uneven = uneven_pack(s, s.total_k, Nk);
 #define GPA_DKDV(DD, GP)                                                                      \
-    launch_kernel(bwd_dkdv_kernel<DD, GP>, grid, block, st, Q, K, V, dO, TS, Z, dK, dV, dKp, \
-                  dVp, s.BH, s.N, s.causal, s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k,       \
-                  s.total_k, Nk, nullptr, nullptr, nullptr, nullptr, nullptr)
+    launch_kernel(uneven ? bwd_dkdv_kernel<DD, GP, false, true>                               \
+                         : bwd_dkdv_kernel<DD, GP, false, false>,                             \
+                  grid, block, st, Q, K, V, dO, TS, Z, dK, dV, dKp, dVp, s.BH, s.N, s.causal, \
+                  s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, Nk, nullptr, nullptr, \
+                  nullptr, nullptr, nullptr)
     if (s.d == 64) {
         if (gp) GPA_DKDV(64, true); else GPA_DKDV(64, false);
     } else {

@@ -40,7 +40,7 @@ __device__ __forceinline__ float exp_arg(float x, float m, float c) {
     }
 }
 
-template <int D, bool FMA>
+template <int D, bool FMA, bool UNEVEN>
 __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, float* __restrict__ LSE,
@@ -56,10 +56,12 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
+    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
+    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head: Q, O
     const size_t kvoff = sr.kv0 * D;  // its key/value head
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
 // partial states is needed; the price is that every K and V fragment read from
 // LDS feeds one MFMA instead of two.  Fewer registers per wave allow more
 // waves per SIMD.  The arithmetic per (query, key) is that of fwd_sbs_kernel.
-template <int D, bool FMA>
+template <int D, bool FMA, bool UNEVEN>
 __global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, float* __restrict__ LSE,
@@ -298,10 +300,12 @@ __global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
+    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
+    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
+    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;  // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;
     const size_t kvoff = sr.kv0 * D;
@@ -450,15 +454,18 @@ hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, u
     dim3 grid((unsigned)(s.BH * T)), block(kThreads);
     // d = 64: one 16-query block per wave (measured faster); d = 128: two
     // blocks per wave, whose halved LDS reads matter more there.
-#define GPA_FWD(KERNEL, DD, FM)                                                               \
-    launch_kernel(KERNEL<DD, FM>, grid, block, st, Q, K, V, O, LSE, s.BH, s.N, s.causal,      \
+    const bool uneven = uneven_pack(s, s.total, s.N);
+#define GPA_FWD(KERNEL, DD, FM, UN)                                                           \
+    launch_kernel(KERNEL<DD, FM, UN>, grid, block, st, Q, K, V, O, LSE, s.BH, s.N, s.causal,      \
                   s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk > 0 ? s.Nk : s.N)
     if (s.d == 64) {
-        if (fma_forward) GPA_FWD(fwd_sbs_q16_kernel, 64, true);
-        else GPA_FWD(fwd_sbs_q16_kernel, 64, false);
+        if (fma_forward) GPA_FWD(fwd_sbs_q16_kernel, 64, true, false);
+        else if (uneven) GPA_FWD(fwd_sbs_q16_kernel, 64, false, true);
+        else GPA_FWD(fwd_sbs_q16_kernel, 64, false, false);
     } else {
-        if (fma_forward) GPA_FWD(fwd_sbs_kernel, 128, true);
-        else GPA_FWD(fwd_sbs_kernel, 128, false);
+        if (fma_forward) GPA_FWD(fwd_sbs_kernel, 128, true, false);
+        else if (uneven) GPA_FWD(fwd_sbs_kernel, 128, false, true);
+        else GPA_FWD(fwd_sbs_kernel, 128, false, false);
     }
 #undef GPA_FWD
     return hipGetLastError();

@@ -65,6 +65,14 @@ struct Shape {
     int Nk = 0;                 // longest key run (dense: N)
 };
 
+// Packed sequences of unequal lengths on one side (rows `total`, longest run
+// `longest`): the kernels' UNEVEN instantiations deal them over the XCDs by
+// head and longest first.  Dense batches, and packs whose runs all have the
+// longest one's length, keep the dense order.
+inline bool uneven_pack(const Shape& s, int total, int longest) {
+    return s.cu != nullptr && (int64_t)(s.BH / s.Hq) * longest != total;
+}
+
 // Kernel ids for timing (gpa_profile_*).
 enum KernelId {
     kKFwd = 0,

@@ -318,3 +318,34 @@ def test_varlen_rejects_bad_arguments(gpa):
     with pytest.raises(gpa.GpaError):  # the key side's longest run exceeds its total
         gpa.attn_fwd_varlen(q, k, v, cu, case.max_seqlen, True, case.scale, cu_seqlens_k=cu,
                             max_seqlen_k=case.total + 1)
+
+
+@pytest.mark.parametrize("Hq,Hkv,causal", [(8, 8, True), (16, 2, True), (16, 16, False), (3, 1, True),
+                                           (12, 4, False)])
+def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal):
+    """Packs of unequal runs deal their heads over the XCDs when Hq is a
+    multiple of 8 and rotate the problems otherwise, in groups of sequences:
+    every problem's rows still equal a pack of that sequence alone, bit for bit
+    (more sequences than one group holds, empty and one-row runs among them)."""
+    lens = [1, 300, 64, 0, 129, 5, 190, 63] * 5 + [700, 65]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    g = torch.Generator().manual_seed(Hq)
+    total, d = int(cu[-1]), 64
+
+    def draw(h):
+        return torch.randn(h, total, d, generator=g).to(torch.bfloat16).cuda()
+
+    q, k, v, u = draw(Hq), draw(Hkv), draw(Hkv), draw(Hq)
+
+    def run(a, b):
+        x = [t[:, a:b].contiguous() for t in (q, k, v, u)]
+        c = torch.from_numpy(cu - a if (a, b) == (0, total) else np.array([0, b - a], np.int32)).cuda()
+        m = max(lens) if (a, b) == (0, total) else b - a
+        o, lse = gpa.attn_fwd_varlen(x[0], x[1], x[2], c, m, causal)
+        return (o, lse) + gpa.attn_bwd_varlen(x[0], x[1], x[2], o, lse, x[3], c, m, "gproj", causal)
+
+    whole = run(0, total)
+    for s in (0, 1, 2, 4, 5, 33, 38, 40, 41):
+        a, b = int(cu[s]), int(cu[s + 1])
+        for n, w, p in zip(("O", "LSE", "dQ", "dK", "dV"), whole, run(a, b)):
+            assert torch.equal(w[:, a:b], p), (n, s)
