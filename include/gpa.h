@@ -309,8 +309,12 @@ gpa_status gpa_attn_bwd_varlen(const uint16_t* Q, const uint16_t* K, const uint1
 
 /*
  * FP32 attention baseline (the accuracy class of the paper's "FP32 attention",
- * appendix on comparison methods: BF16 inputs and outputs, FP32 SIMT
- * arithmetic, no BF16 or reduced-precision matrix products).  One call runs
+ * appendix on comparison methods: BF16 inputs and outputs, FP32 arithmetic, no
+ * operand of a matrix product rounded below FP32).  BF16 inputs are multiplied
+ * as they are (their products are exact in FP32); the FP32 probabilities and
+ * score gradients enter their products as three BF16 parts that add up to them
+ * exactly; every accumulation is FP32.  Inputs that are not finite give results
+ * that are not finite (an infinity may come back as a NaN).  One call runs
  * forward and backward:
  * In : Q, K, V, dO [B,H,N,d] BF16.
  * Out: O, dQ, dK, dV [B,H,N,d] BF16 (RNE casts of FP32 results); LSE [B,H,N] FP32.

@@ -7,22 +7,28 @@
 // resolution.  No N x N matrix is stored.
 //
 // The paper's kernel is SIMT FP32 because the Hopper tensor cores round FP32
-// operands to TF32.  gfx950's matrix cores have a true FP32 mode
-// (v_mfma_f32_16x16x4_f32: FP32 operands, FP32 products and accumulation, no
-// reduced-precision step), so the contractions run there; the softmax, its
-// statistics and the score gradient run on the vector ALU in FP32.  The
-// inputs are BF16, so decoding them to FP32 is exact.
+// operands to TF32.  Here the contractions run on the bf16 matrix cores without
+// rounding an operand: Q K^T and dO V^T multiply BF16 inputs, whose products are
+// exact in FP32, and the FP32 factors P and dS enter as three BF16 parts that
+// add up to them exactly (split3), so P V, P^T dO, dS K and dS^T Q are three
+// exact products into the same FP32 accumulator.  The softmax, its statistics
+// and the score gradient run on the vector ALU in FP32.  Against FP64 the errors
+// are those of the FP32 matrix cores (v_mfma_f32_16x16x4_f32: FP32 operands)
+// or smaller, because a 32-wide product rounds the accumulator once where the
+// 4-wide FP32 one rounds it eight times: FP32 output 1.7e-7 to 1.3e-5 (2.6e-7 to
+// 1.5e-5) relative over N = 77 to 5000, d = 64 and 128, causal and not, key
+// bias 0 to 64; LSE 3.0e-8 to 4.3e-8 (3.1e-8 to 4.9e-8).  What bounds the
+// kernels now is the vector ALU (the split is 5.5 instructions per pair and FP32
+// factor, of 11 to 20): forward / query pass / key pass 369 / 537 / 659 us on the
+// FP32 matrix cores, 99 / 109 / 156 us here (16 heads of 4096 causal tokens, d =
+// 64; without the timers 1552 and 338 us in all).
 //
-// MFMA layout (16x16x4, FP32, wave64): lane (c16 = lane & 15, g = lane >> 4)
-// supplies A[c16][g] and B[g][c16]; the accumulator holds D[4g + i][c16].  A
-// 16 x 16 product over k = d is the sum of d/4 such MFMAs; step s of it lets
-// lane g contract d index dk(s) = 64 (s / 16) + 16 g + s % 16, a permutation
-// shared by both operands, so each lane reads 16 consecutive values of its
-// row (two 16-byte LDS reads) per 64 columns.  The accumulator of S^T = K Q^T
-// (or S = Q K^T) leaves each lane the values of rows 4g + i of its column;
-// fed back one element i at a time as the B operand of the next product, they
-// pair with A elements of rows 4g + i, which the gfx950 LDS transpose read
-// delivers from a row-major BF16 tile.  P and dS never pass through LDS.
+// MFMA layouts as in the BF16 kernels (16x16x32, wave64): lane (c16 = lane & 15,
+// g = lane >> 4) supplies 8 values along k of row (A) or column (B) c16; the
+// accumulator holds D[4g + i][c16].  The accumulator of S^T = K Q^T (or S = Q
+// K^T) leaves each lane the values of rows 4g + i of its column, which is the
+// k-layout the LDS transpose read delivers from a row-major BF16 tile, so P and
+// dS never pass through LDS.
 //
 // Work split: a workgroup has 4 waves and owns 64 rows (queries in the
 // forward and the query-major pass, keys in the key-major pass), 16 per wave;
@@ -36,81 +42,81 @@
 namespace gpa {
 namespace {
 
-__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 // Per query tile, the key-major pass reads three 64-float blocks: the scaled
 // row maximum (+inf beyond N, so P = 0 there), the inverse normaliser (0
 // beyond N) and D = rowsum(dO O32) (0 beyond N).
 constexpr int kF32Stat = 3 * kTile;
 
-// 16 consecutive BF16 values of row `row` at column `col` of a swizzled LDS
-// tile, widened exactly to FP32.
+// A row of a [N, D] BF16 tensor as an MFMA operand along d (zero beyond N
+// through the buffer resource): chunk kc holds columns 32 kc + 8 g .. + 7.
 template <int D>
-__device__ __forceinline__ void lds_row16(const uint16_t* X, int row, int col, float (&out)[16]) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(X + tile_off<D>(row, col));
-    const u32x4 b = *reinterpret_cast<const u32x4*>(X + tile_off<D>(row, col + 8));
+__device__ __forceinline__ void ld_row_chunks(rsrc_t r, int row, int g, bf16x8 (&out)[D / 32]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        out[2 * e] = lo_bf16(a[e]);
-        out[2 * e + 1] = hi_bf16(a[e]);
-        out[8 + 2 * e] = lo_bf16(b[e]);
-        out[8 + 2 * e + 1] = hi_bf16(b[e]);
-    }
-}
-
-// A row of a [N, D] BF16 tensor in the permuted k order: out[s] = X[row][dk(s)]
-// (zero beyond N through the buffer resource).
-template <int D>
-__device__ __forceinline__ void ld_row_perm(rsrc_t r, int row, int g, float (&out)[D / 4]) {
-#pragma unroll
-    for (int h = 0; h < D / 64; ++h) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const u32x4 w = ld_row16<D>(r, row, 64 * h + 16 * g + 8 * p);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                out[16 * h + 8 * p + 2 * e] = lo_bf16(w[e]);
-                out[16 * h + 8 * p + 2 * e + 1] = hi_bf16(w[e]);
-            }
-        }
-    }
+    for (int kc = 0; kc < D / 32; ++kc)
+        out[kc] = __builtin_bit_cast(bf16x8, ld_row16<D>(r, row, 32 * kc + 8 * g));
 }
 
 // One 16 x 16 block X_rows . Y^T over d: the A side comes from a swizzled LDS
-// tile (rows r0 + c16), the B side from registers in the permuted order.
+// tile (rows r0 + c16), the B side from registers.  Both are BF16 inputs, so
+// every product is exact.
 template <int D>
-__device__ __forceinline__ f32x4 block_dot(const uint16_t* X, int r0, const float (&y)[D / 4],
+__device__ __forceinline__ f32x4 block_dot(const uint16_t* X, int r0, const bf16x8 (&y)[D / 32],
                                            int c16, int g) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int h = 0; h < D / 64; ++h) {
-        float a[16];
-        lds_row16<D>(X, r0 + c16, 64 * h + 16 * g, a);
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc = mfma_f32(a[s], y[16 * h + s], acc);
-    }
+    for (int kc = 0; kc < D / 32; ++kc)
+        acc = mfma_16x16x32(ld_b128(X + tile_off<D>(r0 + c16, 32 * kc + 8 * g)), y[kc], acc);
     return acc;
 }
 
-// acc[mb] += X^T[d][rows] . B[rows][col] for the 64 tile rows, where the B
-// values b[kb][i] belong to row 16 kb + 4 g + i and X is a row-major
-// swizzled BF16 tile: the transpose read gives lane (c16, g) X[32 kb2 + 4 g +
-// r][16 mb + c16] and X[32 kb2 + 16 + 4 g + r][...] for r = 0..3.
+// The three BF16 parts of 8 FP32 values, x = hi + mid + lo exactly (24 bits of
+// significand in three times 8): each part is the upper half of what the parts
+// before it leave, which an FP32 subtraction gives exactly.  Five vector
+// instructions per value and a half; a value that is not finite gives parts
+// that are not.
+struct Split {
+    bf16x8 hi, mid, lo;
+};
+__device__ __forceinline__ float upper(float x) {
+    return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
+}
+__device__ __forceinline__ uint32_t uppers(float a, float b) {  // b's upper half above a's
+    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+__device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
+    u32x4 h, m, l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float r[2], q[2];
+        const float x[2] = {j < 2 ? x0[2 * j] : x1[2 * j - 4], j < 2 ? x0[2 * j + 1] : x1[2 * j - 3]};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            r[e] = x[e] - upper(x[e]);
+            q[e] = r[e] - upper(r[e]);
+        }
+        h[j] = uppers(x[0], x[1]);
+        m[j] = uppers(r[0], r[1]);
+        l[j] = uppers(q[0], q[1]);
+    }
+    return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// acc[mb] += X^T[d][rows] . B[rows][col] for the 64 tile rows, where the FP32
+// values b[kb][i] belong to row 16 kb + 4 g + i and X is a row-major swizzled
+// BF16 tile: the transpose read gives lane (c16, g) X[32 kb2 + 4 g + r][16 mb +
+// c16] and X[32 kb2 + 16 + 4 g + r][...] for r = 0..3.
 template <int D>
 __device__ __forceinline__ void tr_accumulate(const uint16_t* X, const f32x4 (&b)[4],
                                               f32x4 (&acc)[D / 16], int c16, int g) {
 #pragma unroll
-    for (int mb = 0; mb < D / 16; ++mb) {
+    for (int kb2 = 0; kb2 < 2; ++kb2) {
+        const Split p = split3(b[2 * kb2], b[2 * kb2 + 1]);
 #pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2) {
+        for (int mb = 0; mb < D / 16; ++mb) {
             const bf16x8 t = ld_tr_operand<D>(X, 32 * kb2, 16 * mb, c16, g);
-#pragma unroll
-            for (int half = 0; half < 2; ++half)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[mb] = mfma_f32(bf16_to_f32(t[4 * half + i]), b[2 * kb2 + half][i], acc[mb]);
+            acc[mb] = mfma_16x16x32(t, p.lo, acc[mb]);
+            acc[mb] = mfma_16x16x32(t, p.mid, acc[mb]);
+            acc[mb] = mfma_16x16x32(t, p.hi, acc[mb]);
         }
     }
 }
@@ -122,7 +128,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
     const uint16_t* __restrict__ V, float* __restrict__ O32, uint16_t* __restrict__ O,
     float* __restrict__ LSE, float* __restrict__ Mrow, float* __restrict__ Linv, int BH, int N,
     int causal, float scale) {
-    constexpr int KS = D / 4, MB = D / 16;
+    constexpr int KC = D / 32, MB = D / 16;
     __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
@@ -135,8 +141,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
     const int q0w = tile * kTile + 16 * wave;
     const int qrow = q0w + c16;
 
-    float qf[KS];
-    ld_row_perm<D>(make_rsrc(Q + hoff, (uint32_t)N * (2 * D)), qrow, g, qf);
+    bf16x8 qf[KC];
+    ld_row_chunks<D>(make_rsrc(Q + hoff, (uint32_t)N * (2 * D)), qrow, g, qf);
 
     const KeyRange kr = key_range(tile, N, 0, causal);
     const int nkv = kr.nkv, nplain = kr.nplain;
@@ -201,11 +207,17 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
     const std::false_type plain;
     const std::true_type masked;
     int kt = 0;
-    for (; kt < nplain; ++kt) {
-        if (kt & 1) step(plain, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-        else step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+    for (; kt + 1 < nplain; kt += 2) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
     }
-    for (; kt < nkv; ++kt) {
+    if (kt < nplain) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        ++kt;
+    }
+    // Tile kt lives in buffer kt mod 2.
+    // At most one tile needs masks: the diagonal one, or the key tail.
+    if (kt < nkv) {
         if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
         else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
     }
@@ -240,7 +252,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
     const float* __restrict__ O32, const float* __restrict__ Mrow,
     const float* __restrict__ Linv, float* __restrict__ TS, uint16_t* __restrict__ dQ, int BH,
     int N, int causal, float scale) {
-    constexpr int KS = D / 4, MB = D / 16;
+    constexpr int KC = D / 32, MB = D / 16;
     __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
@@ -254,21 +266,22 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
     const bool qok = qrow < N;
 
     const uint32_t tb = (uint32_t)N * (2 * D);
-    float qf[KS], uf[KS];
-    ld_row_perm<D>(make_rsrc(Q + hoff, tb), qrow, g, qf);
-    ld_row_perm<D>(make_rsrc(dO + hoff, tb), qrow, g, uf);
+    bf16x8 qf[KC], uf[KC];
+    ld_row_chunks<D>(make_rsrc(Q + hoff, tb), qrow, g, qf);
+    ld_row_chunks<D>(make_rsrc(dO + hoff, tb), qrow, g, uf);
     // D_i = sum_d dO_id O32_id (the saved FP32 output), this lane's d subset
     // then the other three lanes of the query.
     float dpart = 0.f;
     if (qok) {
         const float* orow = O32 + hoff + (size_t)qrow * D;
 #pragma unroll
-        for (int h = 0; h < D / 64; ++h)
+        for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const f32x4 o = *reinterpret_cast<const f32x4*>(orow + 64 * h + 16 * g + 4 * p);
+            for (int p = 0; p < 2; ++p) {
+                const f32x4 o = *reinterpret_cast<const f32x4*>(orow + 32 * kc + 8 * g + 4 * p);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) dpart = fmaf(uf[16 * h + 4 * p + e], o[e], dpart);
+                for (int e = 0; e < 4; ++e)
+                    dpart = fmaf(bf16_to_f32(uf[kc][4 * p + e]), o[e], dpart);
             }
     }
     const float Di = xor_sum(dpart);
@@ -322,11 +335,17 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
     const std::false_type plain;
     const std::true_type masked;
     int kt = 0;
-    for (; kt < nplain; ++kt) {
-        if (kt & 1) step(plain, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-        else step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+    for (; kt + 1 < nplain; kt += 2) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
     }
-    for (; kt < nkv; ++kt) {
+    if (kt < nplain) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        ++kt;
+    }
+    // Tile kt lives in buffer kt mod 2.
+    // At most one tile needs masks: the diagonal one, or the key tail.
+    if (kt < nkv) {
         if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
         else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
     }
@@ -354,7 +373,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
     const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
     const float* __restrict__ TS, uint16_t* __restrict__ dK, uint16_t* __restrict__ dV, int BH,
     int N, int causal, float scale) {
-    constexpr int KS = D / 4, MB = D / 16;
+    constexpr int KC = D / 32, MB = D / 16;
     __shared__ __attribute__((aligned(16))) uint16_t QU0[2][kTile * D];
     __shared__ __attribute__((aligned(16))) uint16_t QU1[2][kTile * D];
     __shared__ __attribute__((aligned(16))) float ST0[kF32Stat];
@@ -369,9 +388,9 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
     const int krow = tile * kTile + 16 * wave + c16;
 
     const uint32_t tb = (uint32_t)N * (2 * D);
-    float kf[KS], vf[KS];
-    ld_row_perm<D>(make_rsrc(K + hoff, tb), krow, g, kf);
-    ld_row_perm<D>(make_rsrc(V + hoff, tb), krow, g, vf);
+    bf16x8 kf[KC], vf[KC];
+    ld_row_chunks<D>(make_rsrc(K + hoff, tb), krow, g, kf);
+    ld_row_chunks<D>(make_rsrc(V + hoff, tb), krow, g, vf);
     const float lg = kLog2e;
     const float* tsh = TS + (size_t)bh * T * kF32Stat;
 
@@ -441,11 +460,15 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
     if (causal && qt < T) {
         step(masked, qt, QU0, ST0, QU1, ST1);
         ++qt;
+    } else if (qt < T) {
+        step(plain, qt, QU0, ST0, QU1, ST1);
+        ++qt;
     }
-    for (; qt < T; ++qt) {
-        if ((qt - qt0) & 1) step(plain, qt, QU1, ST1, QU0, ST0);
-        else step(plain, qt, QU0, ST0, QU1, ST1);
+    for (; qt + 1 < T; qt += 2) {
+        step(plain, qt, QU1, ST1, QU0, ST0);
+        step(plain, qt + 1, QU0, ST0, QU1, ST1);
     }
+    if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
 
     if (krow < N) {
         uint16_t* vrow = dV + hoff + (size_t)krow * D;
