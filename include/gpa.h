@@ -294,6 +294,28 @@ gpa_status gpa_attn_fwd_varlen(const uint16_t* Q, const uint16_t* K, const uint1
                                int64_t max_seqlen_k, int64_t d, int causal, float scale,
                                void* stream);
 
+/*
+ * gpa_attn_fwd_varlen with a workspace, for few queries on long key runs (new
+ * tokens against their past): the keys of such a call are split over several
+ * workgroups and the heads of a group share one pass over K and V.  Whether a
+ * shape is one is decided from its sizes: gpa_attn_fwd_varlen_workspace_bytes
+ * returns the bytes it needs, or 0 where the call is gpa_attn_fwd_varlen itself
+ * (which it then is, bit for bit, and workspace may be NULL).  Same arguments,
+ * arithmetic per (query, key) and errors otherwise; the FP32 sums are taken in
+ * another order.  workspace: at least that many bytes, 256-byte aligned, not
+ * overlapping any other buffer; its contents do not matter.
+ */
+size_t gpa_attn_fwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_t total_k,
+                                           int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
+                                           int64_t max_seqlen_k, int64_t d);
+
+gpa_status gpa_attn_fwd_varlen_ws(const uint16_t* Q, const uint16_t* K, const uint16_t* V,
+                                  uint16_t* O, float* LSE, const int32_t* cu_seqlens_q,
+                                  const int32_t* cu_seqlens_k, int64_t nseq, int64_t total_q,
+                                  int64_t total_k, int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
+                                  int64_t max_seqlen_k, int64_t d, int causal, float scale,
+                                  void* workspace, size_t workspace_bytes, void* stream);
+
 size_t gpa_attn_bwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_t total_k,
                                            int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
                                            int64_t max_seqlen_k, int64_t d, int mode);

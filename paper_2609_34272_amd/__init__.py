@@ -81,6 +81,10 @@ def lib():
                                    INT, P, SZ, P]
     L.gpa_attn_fwd_varlen.restype = INT
     L.gpa_attn_fwd_varlen.argtypes = [P] * 7 + [I64] * 8 + [INT, F32, P]
+    L.gpa_attn_fwd_varlen_workspace_bytes.restype = SZ
+    L.gpa_attn_fwd_varlen_workspace_bytes.argtypes = [I64] * 8
+    L.gpa_attn_fwd_varlen_ws.restype = INT
+    L.gpa_attn_fwd_varlen_ws.argtypes = [P] * 7 + [I64] * 8 + [INT, F32, P, SZ, P]
     L.gpa_attn_bwd_varlen_workspace_bytes.restype = SZ
     L.gpa_attn_bwd_varlen_workspace_bytes.argtypes = [I64] * 8 + [INT]
     L.gpa_attn_bwd_varlen.restype = INT
@@ -351,6 +355,15 @@ def attn_fwd_varlen(q, k, v, cu_seqlens, max_seqlen: int, causal: bool = True, s
         _need(t, n, (pk.Hkv, pk.total_k, pk.d), torch.bfloat16)
     o = torch.empty_like(q)
     lse = torch.empty((pk.Hq, pk.total_q), dtype=torch.float32, device=q.device)
+    # few queries on long key runs: the keys are split, in a workspace
+    nbytes = 0 if pk.max_k < 2048 else int(lib().gpa_attn_fwd_varlen_workspace_bytes(
+        pk.nseq, pk.total_q, pk.total_k, pk.Hq, pk.Hkv, pk.max_q, pk.max_k, pk.d))
+    if nbytes:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
+        _check(lib().gpa_attn_fwd_varlen_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                            lse.data_ptr(), *pk.offsets(), int(bool(causal)),
+                                            _scale(pk.d, scale), ws.data_ptr(), nbytes, _stream(q)))
+        return o, lse
     _check(lib().gpa_attn_fwd_varlen(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                      lse.data_ptr(), *pk.offsets(), int(bool(causal)),
                                      _scale(pk.d, scale), _stream(q)))

@@ -339,6 +339,19 @@ BwdLayout varlen_layout(const Varlen& v, int mode) {
     return bwd_layout_rows((size_t)v.Hq * v.total_q, (size_t)v.Hq * v.total_k,
                            (size_t)v.nseq * v.Hq, v.max_q, v.d, mode, v.Hq > v.Hkv);
 }
+// Workspace of the forward for few queries on long key runs: per split the FP32
+// O accumulators over the query-head rows, then row maximum and row sum.
+struct FewLayout {
+    size_t oacc, ml, total;
+};
+FewLayout few_layout(const Varlen& v, int splits) {
+    const size_t rows = (size_t)splits * v.Hq * v.total_q;
+    FewLayout L;
+    L.oacc = 0;
+    L.ml = round_up(rows * (size_t)v.d * sizeof(float));
+    L.total = L.ml + round_up(2 * rows * sizeof(float));
+    return L;
+}
 // Fused FP32 baseline workspace: the saved FP32 output O32 [B,H,N,d], the
 // scaled row maximum and the inverse normaliser [B,H,N] each, and the
 // per-tile statistics the key-major pass stages ([B*H, T, 3, 64]).
@@ -595,6 +608,60 @@ gpa_status gpa_attn_fwd_varlen(const uint16_t* Q, const uint16_t* K, const uint1
                     "fwd_sbs");
 }
 
+size_t gpa_attn_fwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_t total_k,
+                                           int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
+                                           int64_t max_seqlen_k, int64_t d) {
+    // the same validity as the backward's workspace query
+    if (gpa_attn_bwd_varlen_workspace_bytes(nseq, total_q, total_k, Hq, Hkv, max_seqlen_q,
+                                            max_seqlen_k, d, 0) == 0)
+        return 0;
+    static const int32_t some = 0;  // marks the shape as packed; never read
+    const Varlen v{&some, &some, nseq, total_q, total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d};
+    const int n = gpa::few_splits(varlen_shape(v, 1, 1.f));
+    return n ? few_layout(v, n).total : 0;
+}
+
+gpa_status gpa_attn_fwd_varlen_ws(const uint16_t* Q, const uint16_t* K, const uint16_t* V,
+                                  uint16_t* O, float* LSE, const int32_t* cu_seqlens_q,
+                                  const int32_t* cu_seqlens_k, int64_t nseq, int64_t total_q,
+                                  int64_t total_k, int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
+                                  int64_t max_seqlen_k, int64_t d, int causal, float scale,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+    const Varlen v{cu_seqlens_q, cu_seqlens_k ? cu_seqlens_k : cu_seqlens_q, nseq, total_q,
+                   total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d};
+    gpa_status s = check_varlen(v, scale);
+    if (s != GPA_OK) return s;
+    const gpa::Shape sh = varlen_shape(v, causal, scale);
+    const int n = gpa::few_splits(sh);
+    if (n == 0)
+        return gpa_attn_fwd_varlen(Q, K, V, O, LSE, cu_seqlens_q, cu_seqlens_k, nseq, total_q,
+                                   total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d, causal, scale,
+                                   stream);
+    const FewLayout L = few_layout(v, n);
+    if (!workspace || workspace_bytes < L.total)
+        return fail(GPA_EWORKSPACE, "workspace %p of %zu bytes; %zu needed", workspace,
+                    workspace_bytes, L.total);
+    if ((uintptr_t)workspace % kAlign)
+        return fail(GPA_EWORKSPACE, "workspace is not %zu-byte aligned", kAlign);
+    const size_t tq = (size_t)Hq * total_q * d * 2, tkv = (size_t)Hkv * total_k * d * 2;
+    const size_t lb = (size_t)Hq * total_q * 4;
+    const std::vector<Buf> outs = {{O, tq, "O"}, {LSE, lb, "LSE"}, {workspace, L.total, "workspace"}};
+    s = check_ptrs({{Q, tq, "Q"}, {K, tkv, "K"}, {V, tkv, "V"}}, outs);
+    if (s != GPA_OK) return s;
+    if ((s = check_cu_overlap(v, outs)) != GPA_OK) return s;
+    hipStream_t st = (hipStream_t)stream;
+    char* ws = (char*)workspace;
+    float* oacc = (float*)(ws + L.oacc);
+    float* ml = (float*)(ws + L.ml);
+    s = launched(timed(gpa::kKFwdFew,
+                       [&] { return gpa::launch_fwd_few(Q, K, V, oacc, ml, n, sh, st); }),
+                 "fwd_few");
+    if (s != GPA_OK) return s;
+    return launched(timed(gpa::kKFwdFewMerge,
+                          [&] { return gpa::launch_fwd_few_merge(oacc, ml, O, LSE, n, sh, st); }),
+                    "fwd_few_merge");
+}
+
 size_t gpa_attn_bwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_t total_k,
                                            int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,
                                            int64_t max_seqlen_k, int64_t d, int mode) {
@@ -714,7 +781,8 @@ int gpa_profile_read(double* total_ms, int64_t* launches, int n) {
 const char* gpa_kernel_name(int id) {
     static const char* names[gpa::kNumKernels] = {
         "fwd_sbs",   "bwd_dq",  "bwd_dkdv",        "fp32_fwd",       "fp32_dq",
-        "fp32_dkdv", "group_sum", "bwd_pre", "bwd_fused", "bwd_dq_finalize", "bwd_dk_corr"};
+        "fp32_dkdv", "group_sum", "bwd_pre", "bwd_fused", "bwd_dq_finalize", "bwd_dk_corr",
+        "fwd_few",   "fwd_few_merge"};
     return (id >= 0 && id < gpa::kNumKernels) ? names[id] : "";
 }
 

@@ -446,7 +446,270 @@ __global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
     }
 }
 
+// Few queries against long key runs (packed sequences; the rule and the number
+// of splits are few_splits' in gpa_launch.h).  A workgroup of the kernels above
+// would fill a few of its 64 query rows and walk every key tile alone, and each
+// query head would read its group's K and V again.  Here the rows of a
+// (sequence, key/value head) are all G heads' queries (row r: head r / nq, query
+// r % nq), so K and V are read once per group, and the key tiles are split over
+// S workgroups, each leaving its unnormalised state (O^T accumulator, row
+// maximum, row sum; FP32) in the workspace for fwd_few_merge_kernel.  Per
+// (query, key) the arithmetic is fwd_sbs_q16_kernel's, and the states merge by
+// the rescale rule it uses between tiles.  What bounds it: the latency of each
+// split's few tiles, then HBM; 8 sequences of 4 queries on 406 to 5115 keys, 16
+// heads on 4, d = 128 (47 MB of K and V): 68.7 us before, 17 us with the merge.
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void fwd_few_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, float* __restrict__ Oacc, float* __restrict__ ML, int Nmax,
+    int causal, float scale, int G, const int* __restrict__ cu, int Hq, int total,
+    const int* __restrict__ cu_k, int total_k, int Nkmax, int S) {
+    constexpr int MB = D / 16;
+    constexpr int KC = D / 32;
+    __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
+    __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
+
+    // blockIdx: split fastest, then row tile, then (sequence, key/value head)
+    const int RT = (G * Nmax + kTile - 1) / kTile;
+    const int split = blockIdx.x % S;
+    const int rest = blockIdx.x / S;
+    const int rt = rest % RT, prob = rest / RT;
+    const int Hkv = Hq / G;
+    const int seq = prob / Hkv, kvh = prob - seq * Hkv;
+    const SeqRows sr = seq_rows(cu, cu_k, seq * Hq + kvh * G, Nmax, Nkmax, G, Hq, total, total_k);
+    const int N = sr.nq, Nk = sr.nk;
+    const int rows = G * N;
+    if (rt * kTile >= rows) return;
+    const int off = Nk - N;
+    const size_t kvoff = sr.kv0 * D;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c16 = lane & 15;
+    const int r = rt * kTile + 16 * wave + c16;  // this lane's row
+    const bool active = rt * kTile + 16 * wave < rows;  // the wave has a row
+    const int hg = r / N, qi = r - hg * N;       // its head in the group and query
+    const size_t qrow = sr.q0 + (size_t)hg * total + qi;  // its row of Q, O and LSE
+
+    bf16x8 qf[KC];
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+        u32x4 w = {0u, 0u, 0u, 0u};
+        if (r < rows) w = *reinterpret_cast<const u32x4*>(Q + qrow * D + kc * 32 + 8 * g);
+        qf[kc] = __builtin_bit_cast(bf16x8, w);
+    }
+    const float c = scale * kLog2e;
+    float mrun = -INFINITY, lrun = 0.f;
+    f32x4 acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Key tiles of the sequence, of this split, and the first that needs masks
+    // (every query sees the keys up to the first query's last one).
+    const int tiles = (Nk + kTile - 1) / kTile;
+    const int chunk = (tiles + S - 1) / S;
+    const int kt0 = min(split * chunk, tiles), kt1 = min(kt0 + chunk, tiles);
+    const int nplain = min(causal ? max(floor_div(off + 1, kTile), 0) : Nk / kTile, Nk / kTile);
+
+    TileDma<D> dma;
+    dma.init(lane, wave);
+    wait_vm_lgkm0<0>();
+    if (kt0 < kt1) {
+        dma.load(K + kvoff, KV0[0], kt0 * kTile, Nk);
+        dma.load(V + kvoff, KV0[1], kt0 * kTile, Nk);
+    }
+    wait_vm_lgkm0<0>();
+    __builtin_amdgcn_s_barrier();
+
+    auto compute = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc) {
+        constexpr bool MASK = decltype(masked)::value;
+        f32x4 s[4];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc)
+                s[kb] = mfma_16x16x32(ld_b128(Kc + tile_off<D>(kb * 16 + c16, kc * 32 + 8 * g)),
+                                      qf[kc], s[kb]);
+        }
+        if constexpr (MASK) {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int key = kt * kTile + kb * 16 + 4 * g + i;
+                    const bool ok = key < Nk && (!causal || key <= qi + off);
+                    s[kb][i] = ok ? s[kb][i] : -INFINITY;
+                }
+        }
+        float mx = s[0][0];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kb][i]);
+        mx = xor_max(mx);
+        const float mnew = fmaxf(mrun, mx);
+        const float ms = (mnew == -INFINITY) ? 0.f : mnew;
+        if (__builtin_amdgcn_ballot_w64(mnew != mrun) != 0) {
+            const float corr = fexp2((mrun - ms) * c);
+            lrun *= corr;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
+        }
+        bf16x8 pf[2];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float z = fexp2(exp_arg<false>(s[kb][i], ms, c));
+                lrun += z;
+                pf[kb >> 1][(kb & 1) * 4 + i] = to_bf16(z);
+            }
+        mrun = mnew;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[mb] = mfma_16x16x32(ld_tr_operand<D>(Vc, 32 * j, mb * 16, c16, g), pf[j],
+                                        acc[mb]);
+    };
+    auto step = [&](int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn, uint16_t* Vn) {
+        if (kt + 1 < kt1) {
+            dma.load(K + kvoff, Kn, (kt + 1) * kTile, Nk);
+            dma.load(V + kvoff, Vn, (kt + 1) * kTile, Nk);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (active) {
+            if (kt < nplain) compute(std::false_type{}, kt, Kc, Vc);
+            else compute(std::true_type{}, kt, Kc, Vc);
+        }
+        wait_vm_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();
+    };
+    for (int kt = kt0; kt < kt1; kt += 2) {
+        step(kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        if (kt + 1 < kt1) step(kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+    }
+
+    const float ltot = xor_sum(lrun);
+    if (r < rows) {
+        const size_t p = (size_t)split * ((size_t)Hq * total) + qrow;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            *reinterpret_cast<f32x4*>(Oacc + p * D + mb * 16 + 4 * g) = acc[mb];
+        if (g == 0) {
+            ML[2 * p] = mrun;
+            ML[2 * p + 1] = ltot;
+        }
+    }
+}
+
+// Merges the S <= kFewMaxSplits states of every row by the forward's rescale
+// rule and finishes as it does.  D/4 lanes share a row, 4 columns each: they read
+// the row maxima and sums of different splits at once and leave the weights in
+// LDS, then read the accumulators eight splits at a time, so the pass waits for
+// two round trips to memory and not for 2 S (20 us for 32 splits one after the
+// other, 6 us so).  A split that saw none of the row's keys has l = 0 (on the bits,
+// as in the kernels above); its weight is marked -1 and its accumulator, which
+// may hold anything, is not used.
+template <int D>
+__global__ __launch_bounds__(256) void fwd_few_merge_kernel(
+    const float* __restrict__ Oacc, const float* __restrict__ ML, uint16_t* __restrict__ O,
+    float* __restrict__ LSE, int Nmax, float scale, const int* __restrict__ cu, int Hq, int total,
+    int chunks, int S) {
+    constexpr int LPR = D / 4;         // lanes of a row
+    constexpr int RPB = 256 / LPR;     // rows of a workgroup
+    constexpr int MPL = kFewMaxSplits / LPR;
+    __shared__ float W[RPB][kFewMaxSplits];
+    const int prob = blockIdx.x / chunks;
+    const int rl = threadIdx.x / LPR, j = threadIdx.x - rl * LPR;
+    const int qi = (blockIdx.x - prob * chunks) * RPB + rl, col = 4 * j;
+    const int seq = prob / Hq, h = prob - seq * Hq;
+    const int a = min(max(cu[seq], 0), total);
+    const int b = min(max(cu[seq + 1], a), total);
+    const bool have = qi < min(b - a, Nmax);
+    const size_t rows = (size_t)Hq * total;
+    const size_t row = (size_t)h * total + a + (have ? qi : 0);
+    const float c = scale * kLog2e;
+    float ms[MPL], ls[MPL], m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < MPL; ++i) {
+        const int sp = j + i * LPR;
+        ms[i] = -INFINITY;
+        ls[i] = 0.f;
+        if (have && sp < S) {
+            ms[i] = ML[2 * (sp * rows + row)];
+            ls[i] = ML[2 * (sp * rows + row) + 1];
+        }
+        m = fmaxf(m, ms[i]);
+    }
+#pragma unroll
+    for (int x = 1; x < LPR; x *= 2) m = fmaxf(m, __shfl_xor(m, x));
+    const float msub = (m == -INFINITY) ? 0.f : m;
+    float l = 0.f;
+#pragma unroll
+    for (int i = 0; i < MPL; ++i) {
+        const bool seen = __float_as_uint(ls[i]) != 0u;
+        const float f = fexp2((ms[i] - msub) * c);
+        W[rl][j + i * LPR] = seen ? f : -1.f;
+        l += seen ? ls[i] * f : 0.f;
+    }
+#pragma unroll
+    for (int x = 1; x < LPR; x *= 2) l += __shfl_xor(l, x);
+    __syncthreads();
+    if (!have) return;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < S; s0 += 8) {
+        f32x4 x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s0 + i < S)
+                x[i] = *reinterpret_cast<const f32x4*>(Oacc + ((s0 + i) * rows + row) * D + col);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (s0 + i >= S) break;
+            const float w = W[rl][s0 + i];
+            if (__float_as_uint(w) != 0xBF800000u) o += x[i] * w;
+        }
+    }
+    const bool empty = __float_as_uint(l) == 0u;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = empty ? 0.f : o[i] / l;
+    st_bf16x4(O + row * D + col, v[0], v[1], v[2], v[3]);
+    if (j == 0) {
+#pragma clang fp contract(off)
+        const float lse = scale * m + logf(l);
+        LSE[row] = empty ? INFINITY : lse;
+    }
+}
+
 }  // namespace
+
+hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, float* Oacc,
+                          float* ML, int splits, const Shape& s, hipStream_t st) {
+    const int RT = (s.G * s.N + kTile - 1) / kTile;
+    dim3 grid((unsigned)(s.BH / s.G * RT * splits)), block(kThreads);
+#define GPA_FEW(DD)                                                                            \
+    launch_kernel(fwd_few_kernel<DD>, grid, block, st, Q, K, V, Oacc, ML, s.N, s.causal,       \
+                  s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk, splits)
+    if (s.d == 64) GPA_FEW(64); else GPA_FEW(128);
+#undef GPA_FEW
+    return hipGetLastError();
+}
+
+hipError_t launch_fwd_few_merge(const float* Oacc, const float* ML, uint16_t* O, float* LSE,
+                                int splits, const Shape& s, hipStream_t st) {
+    const int chunks = (s.N * (s.d / 4) + 255) / 256;  // workgroups of 1024 / d rows
+    dim3 grid((unsigned)(s.BH * chunks)), block(256);
+    if (s.d == 64)
+        launch_kernel(fwd_few_merge_kernel<64>, grid, block, st, Oacc, ML, O, LSE, s.N, s.scale,
+                      s.cu, s.Hq, s.total, chunks, splits);
+    else
+        launch_kernel(fwd_few_merge_kernel<128>, grid, block, st, Oacc, ML, O, LSE, s.N, s.scale,
+                      s.cu, s.Hq, s.total, chunks, splits);
+    return hipGetLastError();
+}
 
 hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
                       float* LSE, const Shape& s, hipStream_t st, bool fma_forward) {

@@ -73,6 +73,30 @@ inline bool uneven_pack(const Shape& s, int total, int longest) {
     return s.cu != nullptr && (int64_t)(s.BH / s.Hq) * longest != total;
 }
 
+// Splits of the key tiles in the forward for few queries on long key runs of
+// packed sequences (fwd_few_kernel), or 0 where the ordinary forward runs.  It
+// takes at most 128 queries on at least 2048 keys, eight times as many keys as
+// queries (longest runs), where either the workgroups are too few to fill the
+// chip (then as many splits as bring them to kFewTarget, four key tiles or more
+// each) or a group of heads has rows for one 64-row tile at most and would read
+// its K and V once per head.  Measured, ordinary and split, us: 8 sequences of 4
+// queries on up to 5115 keys, 16 heads on 4, d = 128: 69 and 17; 4 of 128 on up
+// to 8192, 8 heads: 112 and 33; 24 of 1 on 8192, 32 heads on 8: 298 and 150; 16
+// of 64 on up to 2048, 16 heads on 4, d = 64: 22.6 and 20.1; with 24 of 16 on up
+// to 1024, 32 heads on 8, 14.2 and 18.3: the line at 2048 keys.  kFewTarget 512
+// is up to 18 % slower than 1024 where a sequence has few splits.
+constexpr int kFewMaxSplits = 32;
+inline int few_splits(const Shape& s) {
+    constexpr int64_t kFewTarget = 1024;
+    if (s.cu == nullptr || s.N > 128 || s.Nk < 2048 || s.Nk < 8 * s.N) return 0;
+    const int64_t base = (int64_t)(s.BH / s.G) * ((s.G * s.N + 63) / 64);
+    const int64_t most = (s.Nk + 255) / 256;
+    int64_t n = (kFewTarget + base - 1) / base;
+    if (n > most) n = most;
+    if (n > kFewMaxSplits) n = kFewMaxSplits;
+    return n >= 2 || (s.G > 1 && s.G * s.N <= 64) ? (int)n : 0;
+}
+
 // Kernel ids for timing (gpa_profile_*).
 enum KernelId {
     kKFwd = 0,
@@ -86,12 +110,22 @@ enum KernelId {
     kKBwdFused = 8,
     kKBwdFinal = 9,
     kKBwdCorr = 10,
-    kNumKernels = 11
+    kKFwdFew = 11,
+    kKFwdFewMerge = 12,
+    kNumKernels = 13
 };
 
 // fma_forward selects the historical exponent rounding (diagnostic only).
 hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
                       float* LSE, const Shape& s, hipStream_t st, bool fma_forward = false);
+
+// Forward for few queries on long key runs: per split the FP32 accumulators
+// Oacc [splits, Hq, total, d] and the row maximum and sum ML [splits, Hq, total,
+// 2]; the second launcher merges them into O and LSE.
+hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, float* Oacc,
+                          float* ML, int splits, const Shape& s, hipStream_t st);
+hipError_t launch_fwd_few_merge(const float* Oacc, const float* ML, uint16_t* O, float* LSE,
+                                int splits, const Shape& s, hipStream_t st);
 
 // Query-major pass: writes D = rowsum(dO * O) and dQ; in the gproj modes also
 // rho, m, lambda (zero in plain mode); in gproj mode also Z = BF16(-lambda Q)

@@ -349,3 +349,48 @@ def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal):
         a, b = int(cu[s]), int(cu[s + 1])
         for n, w, p in zip(("O", "LSE", "dQ", "dK", "dV"), whole, run(a, b)):
             assert torch.equal(w[:, a:b], p), (n, s)
+
+
+@pytest.mark.parametrize("newq,Hq,Hkv,d,causal", [
+    (1, 4, 4, 64, True), (4, 16, 4, 128, True), (5, 12, 4, 64, True), (16, 4, 1, 128, False),
+    (17, 4, 1, 64, True), (33, 4, 2, 128, True), (128, 2, 1, 64, True), (3, 8, 2, 64, False)])
+def test_few_queries_on_long_keys(gpa, newq, Hq, Hkv, d, causal):
+    """The split forward for few queries on long key runs, against FP64 and the
+    ordinary forward: row tiles that end inside a head, splits without keys,
+    sequences with fewer keys than queries, none of either, and key tails."""
+    lens_q = [newq, newq, max(1, newq // 2), 0, newq, newq]
+    lens_k = [2100, 64, 999, 300, 0, max(1, newq - 1)]
+    cu = np.concatenate([[0], np.cumsum(lens_q)]).astype(np.int32)
+    ck = np.concatenate([[0], np.cumsum(lens_k)]).astype(np.int32)
+    g = torch.Generator().manual_seed(newq + d)
+    q, k, v = (torch.randn(h, int(t), d, generator=g).to(torch.bfloat16).cuda()
+               for h, t in ((Hq, cu[-1]), (Hkv, ck[-1]), (Hkv, ck[-1])))
+    dcu, dck = torch.from_numpy(cu).cuda(), torch.from_numpy(ck).cuda()
+    args = (len(lens_q), int(cu[-1]), int(ck[-1]), Hq, Hkv, max(lens_q), max(lens_k), d)
+    assert gpa.lib().gpa_attn_fwd_varlen_workspace_bytes(*args) > 0
+    o, lse = gpa.attn_fwd_varlen(q, k, v, dcu, max(lens_q), causal, cu_seqlens_k=dck,
+                                 max_seqlen_k=max(lens_k))
+    o1, lse1 = torch.empty_like(o), torch.empty_like(lse)
+    scale = float(np.float32(1 / np.sqrt(d)))
+    assert gpa.lib().gpa_attn_fwd_varlen(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), o1.data_ptr(), lse1.data_ptr(), dcu.data_ptr(),
+        dck.data_ptr(), *args, int(causal), scale, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    for s in range(len(lens_q)):
+        a, b, ka, kb = (int(x) for x in (cu[s], cu[s + 1], ck[s], ck[s + 1]))
+        for h in range(Hq):
+            K, V = (t[h // (Hq // Hkv), ka:kb].double().cpu() for t in (k, v))
+            x = q[h, a:b].double().cpu() @ K.T * scale
+            if causal:
+                i, j = torch.arange(b - a)[:, None], torch.arange(kb - ka)[None, :]
+                x.masked_fill_(j > i + (kb - ka) - (b - a), -float("inf"))
+            seen = torch.isfinite(x).any(1) if kb > ka else torch.zeros(b - a, dtype=torch.bool)
+            ho, hl = o[h, a:b].double().cpu(), lse[h, a:b].double().cpu()
+            assert (ho[~seen] == 0).all() and torch.isposinf(hl[~seen]).all()
+            if not seen.any():
+                continue
+            # casts of P and O (2^-9 each, of values that average), as everywhere
+            e = torch.softmax(x[seen], 1) @ V
+            assert (ho[seen] - e).norm() <= 5e-3 * e.norm()
+            assert (hl[seen] - torch.logsumexp(x[seen], 1)).abs().max() <= 1e-5
+            assert (ho - o1[h, a:b].double().cpu()).norm() <= 5e-3 * e.norm()
