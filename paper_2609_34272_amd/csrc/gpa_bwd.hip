@@ -820,10 +820,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     // A key tile that no query sees (qt0 >= T) takes no step and stores zeros.
     if (qt0 < T) step(masked, qt0, B0, B2);
     if (qt0 + 1 < T) step(masked, qt0 + 1, B1, B0);
-    // Pin where the loop's code starts: 16 bytes into a 32-byte window.  The
-    // same instructions run 88 us there and 92 (0 bytes) to 95 us (24 bytes) at
-    // h16_n4096_d64 gproj; without this, any edit before the loop moves it.
-    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    // Pin where the loop's code starts, at a 32-byte window: the same
+    // instructions run 87 us there and 88, 89 and 91 us at 24, 16 and 8 bytes
+    // (h16_n4096_d64 gproj); without this, any edit before the loop moves it.
+    asm volatile(".p2align 5");
     for (int qt = qt0 + 2; qt < T; qt += 3) {
         step(plain, qt, B2, B1);
         if (qt + 1 < T) step(plain, qt + 1, B0, B2);

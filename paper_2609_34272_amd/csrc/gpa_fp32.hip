@@ -20,8 +20,8 @@
 // bias 0 to 64; LSE 3.0e-8 to 4.3e-8 (3.1e-8 to 4.9e-8).  What bounds the
 // kernels now is the vector ALU (the split is 5.5 instructions per pair and FP32
 // factor, of 11 to 20): forward / query pass / key pass 369 / 537 / 659 us on the
-// FP32 matrix cores, 99 / 109 / 156 us here (16 heads of 4096 causal tokens, d =
-// 64; without the timers 1552 and 338 us in all).
+// FP32 matrix cores, 85 / 96 / 136 us here (16 heads of 4096 causal tokens, d =
+// 64; 1552 and 316 us in all).
 //
 // MFMA layouts as in the BF16 kernels (16x16x32, wave64): lane (c16 = lane & 15,
 // g = lane >> 4) supplies 8 values along k of row (A) or column (B) c16; the
