@@ -76,6 +76,38 @@ __device__ __forceinline__ void pair_reduce(float (&v)[NV], float* scratch, int 
     }
 }
 
+// The exchange that ends the two main passes: the two waves that hold partial
+// sums of the same rows each finish half of them.  A wave parks the half that its
+// partner finishes (theirs) and adds what the partner parked to its own half
+// (a + b and b + a are the same bits).  Of the NW waves' W0 values per lane the
+// first NW/2 waves' lie in the LDS object `lo` and the others' in `hi`; W1 more
+// per wave lie in `rest`; a round moves W0 + W1 values.  The caller has
+// synchronised the workgroup, so the objects are free.
+template <int NV, int NW, int W0, int W1>
+__device__ __forceinline__ void pair_exchange(float (&mine)[NV], const float (&theirs)[NV],
+                                              void* lo, void* hi, void* rest, int wave, int mate,
+                                              int lane) {
+    auto at0 = [&](int w) {
+        return reinterpret_cast<float*>(w < NW / 2 ? lo : hi) + (w % (NW / 2)) * 64 * W0 + lane;
+    };
+    auto at1 = [&](int w) { return reinterpret_cast<float*>(rest) + w * 64 * W1 + lane; };
+    constexpr int PER = W0 + W1;
+#pragma unroll
+    for (int j0 = 0; j0 < NV; j0 += PER) {
+        if (j0) __syncthreads();  // the round before has been read
+        float *p0 = at0(wave), *p1 = at1(wave);
+#pragma unroll
+        for (int j = j0; j < (j0 + PER < NV ? j0 + PER : NV); ++j)
+            *(j - j0 < W0 ? p0 + (j - j0) * 64 : p1 + (j - j0 - W0) * 64) = theirs[j];
+        __syncthreads();
+        p0 = at0(mate);
+        p1 = at1(mate);
+#pragma unroll
+        for (int j = j0; j < (j0 + PER < NV ? j0 + PER : NV); ++j)
+            mine[j] += *(j - j0 < W0 ? p0 + (j - j0) * 64 : p1 + (j - j0 - W0) * 64);
+    }
+}
+
 // --------------------------------------------------------- query-major pass
 // P, r, t of one 32-key x 16-query block pair: s[kb], dp[kb] hold keys
 // 4g+i of key block kb for this lane's query.  MASK applies the causal and
@@ -117,7 +149,6 @@ void bwd_dq_kernel(
     int Nkmax) {
     constexpr int MB = D / 16;  // 16-column blocks of d
     constexpr int KC = D / 32;  // 32-wide k chunks of d
-    constexpr int PER_NB = 2 * MB * 4 + 2;  // partial A, B (interleaved) and rho, m
     // NB 16-row query blocks per wave: QG groups of waves own the 64 rows,
     // two waves (the two key halves of each tile) per group.
     constexpr int QG = 4 / NB;
@@ -323,54 +354,71 @@ void bwd_dq_kernel(
     wait_vm_lgkm0<0>();
     __builtin_amdgcn_s_barrier();
 
-    // Add the partials of the two waves that own the same queries (one query
-    // block at a time, to bound the LDS the exchange needs).
-    float red[NB][PER_NB];
+    // Add the partials of the two waves that own the same queries.  Each wave
+    // finishes half of what the pair owns: query block kh of two, or, with one
+    // block per wave, half kh of the column blocks.  With one wave of each pair
+    // finishing both halves, block by block in rounds of 32 values (12 barriers
+    // where this takes 1 or 3), the gproj pass took 31.5 us where it takes 30.0 (4
+    // x 8 heads of 1000 tokens, d = 128), 21.5 and 19.6 (16 x 8 heads on 2 of 200,
+    // d = 128), 7.5 and 6.9 (one head of 128, d = 64); long sequences gain 0.5 to
+    // 2 %.
+    constexpr int HB = NB == 2 ? MB : MB / 2;  // column blocks of a half
+    constexpr int NV = GPROJ ? 2 + 8 * HB : 4 * HB;
+    float red[2][NV];  // per half: rho, m, A and B interleaved (plain: A)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+    for (int hf = 0; hf < 2; ++hf) {
+        const int nb = NB == 2 ? hf : 0, mb0 = NB == 2 ? 0 : hf * HB;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < HB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                red[nb][(mb * 4 + i) * 2] = accA[nb][mb][i];
-                red[nb][(mb * 4 + i) * 2 + 1] = GPROJ ? accB[nb][mb][i] : 0.f;
-            }
-        red[nb][2 * MB * 4] = accR[nb][0];
-        red[nb][2 * MB * 4 + 1] = accM[nb][0];
-        if (nb) __syncthreads();  // the previous exchange has been read
-        pair_reduce<PER_NB, sizeof(S0) / 4, QG>(red[nb], reinterpret_cast<float*>(S0), wave, lane);
+            for (int i = 0; i < 4; ++i)
+                if constexpr (GPROJ) {
+                    red[hf][2 + (mb * 4 + i) * 2] = accA[nb][mb0 + mb][i];
+                    red[hf][3 + (mb * 4 + i) * 2] = accB[nb][mb0 + mb][i];
+                } else {
+                    red[hf][mb * 4 + i] = accA[nb][mb0 + mb][i];
+                }
+        if constexpr (GPROJ) {
+            red[hf][0] = accR[nb][0];
+            red[hf][1] = accM[nb][0];
+        }
     }
-    if (wave >= QG) return;
-
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+    auto finish = [&](auto half) {
+        constexpr int hf = decltype(half)::value;
+        constexpr int nb = NB == 2 ? hf : 0, mb0 = NB == 2 ? 0 : hf * HB;
+        constexpr int W0 = 32, W1 = 16;
+        static_assert(sizeof(S0) >= (size_t)QG * 64 * W0 * 4 &&
+                          sizeof(S2) >= (size_t)2 * QG * 64 * W1 * 4,
+                      "exchange space");
+        pair_exchange<NV, 2 * QG, W0, W1>(red[hf], red[1 - hf], S0, S1, S2, wave,
+                                          hf ? wave - QG : wave + QG, lane);
         const int qrow = q0w + nb * 16 + c16;
         // rho and m of this lane's query sit in accumulator row 0 (lanes g == 0).
         float lam = 0.f, rho = 0.f, msum = 0.f;
         if (GPROJ) {
-            rho = __shfl(red[nb][2 * MB * 4], c16);
-            msum = __shfl(red[nb][2 * MB * 4 + 1], c16);
+            rho = __shfl(red[hf][0], c16);
+            msum = __shfl(red[hf][1], c16);
             lam = (msum != 0.f) ? rho / msum : 0.f;  // one IEEE FP32 division
         }
         if (qrow < N) {
             uint16_t* drow = dQ + hoff + (size_t)qrow * D;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
+            for (int mb = 0; mb < HB; ++mb) {
                 float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
 #pragma clang fp contract(off)
-                    const float a = red[nb][(mb * 4 + i) * 2];
-                    const float b = red[nb][(mb * 4 + i) * 2 + 1];
-                    if (GPROJ) {
+                    if constexpr (GPROJ) {
+                        const float a = red[hf][2 + (mb * 4 + i) * 2];
+                        const float b = red[hf][3 + (mb * 4 + i) * 2];
                         const float corr = lam * b;
                         const float diff = a - corr;
                         v[i] = scale * diff;
                     } else {
-                        v[i] = scale * a;
+                        v[i] = scale * red[hf][mb * 4 + i];
                     }
                 }
-                st_bf16x4(drow + mb * 16 + 4 * g, v[0], v[1], v[2], v[3]);
+                st_bf16x4(drow + (mb0 + mb) * 16 + 4 * g, v[0], v[1], v[2], v[3]);
             }
             if (WRITE_Z) {
                 // -z = BF16(fl32(-lambda q)) = -BF16(fl32(lambda q)) for the key
@@ -378,7 +426,7 @@ void bwd_dq_kernel(
                 // into the t^T Q accumulator: the lane holds d = kc*32 + 8g .. +7
                 // of its query row.
 #pragma unroll
-                for (int kc = 0; kc < KC; ++kc) {
+                for (int kc = mb0 / 2; kc < (mb0 + HB) / 2; ++kc) {
                     bf16x8 z;
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
@@ -386,7 +434,7 @@ void bwd_dq_kernel(
                     *reinterpret_cast<bf16x8*>(Zout + hoff + (size_t)qrow * D + kc * 32 + 8 * g) = z;
                 }
             }
-            if (g == 0) {
+            if (g == 0 && (NB == 2 || hf == 0)) {
                 D_out[soff + qrow] = Di[nb];
                 rho_out[soff + qrow] = rho;
                 m_out[soff + qrow] = msum;
@@ -395,12 +443,14 @@ void bwd_dq_kernel(
         }
         // The tile's statistics block for the key-major pass: log2-scaled LSE
         // (+inf beyond N), then D (0 beyond N).
-        if (g == 0) {
+        if (g == 0 && (NB == 2 || hf == 0)) {
             float* ts = TS + ((size_t)bh * T + tile) * kStatFloats;
             ts[qrow - tile * kTile] = lse2[nb];
             ts[kTile + qrow - tile * kTile] = Di[nb];
         }
-    }
+    };
+    if (kh == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 1>{});
 }
 
 // ----------------------------------------------------------- key-major pass
@@ -820,10 +870,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     // A key tile that no query sees (qt0 >= T) takes no step and stores zeros.
     if (qt0 < T) step(masked, qt0, B0, B2);
     if (qt0 + 1 < T) step(masked, qt0 + 1, B1, B0);
-    // Pin where the loop's code starts, at a 32-byte window: the same
-    // instructions run 87 us there and 88, 89 and 91 us at 24, 16 and 8 bytes
+    // Pin where the loop's code starts, 16 bytes into a 32-byte window: the same
+    // instructions run 86 us there and 89, 88 and 86 us at 0, 8 and 24 bytes
     // (h16_n4096_d64 gproj); without this, any edit before the loop moves it.
-    asm volatile(".p2align 5");
+    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int qt = qt0 + 2; qt < T; qt += 3) {
         step(plain, qt, B2, B1);
         if (qt + 1 < T) step(plain, qt + 1, B0, B2);
@@ -834,11 +884,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     wait_vm_lgkm0<0>();
     __builtin_amdgcn_s_barrier();
 
-    // Add the partials of the two waves that own the same keys (one key block
-    // at a time, to bound the LDS the exchange needs).
+    // Add the partials of the two waves that own the same keys: wave qh = kb of
+    // the pair finishes key block kb, in one round with one barrier.  With one
+    // wave of each pair finishing both, the gproj pass took 36.4 us where it takes
+    // 34.3 (4 x 8 heads of 1000 tokens, d = 128), 23.9 and 22.0 (16 x 8 heads on 2
+    // of 200, d = 128); no difference at d = 64.
     float red[2][PER_KB];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -847,15 +900,13 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
                 red[kb][j] = accV[kb][mb][i];
                 red[kb][j + 1] = accK[kb][mb][i];
             }
-        if (kb) __syncthreads();  // the previous exchange has been read
-        pair_reduce<PER_KB, sizeof(B0) / 4>(red[kb], reinterpret_cast<float*>(B0), wave, lane);
-    }
-    if (wave >= 2) return;
-
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    auto finish = [&](auto half) {
+        constexpr int kb = decltype(half)::value;
+        static_assert(sizeof(B0) >= (size_t)2 * 64 * PER_KB * 4, "exchange space");
+        pair_exchange<PER_KB, kWaves, PER_KB, 0>(red[kb], red[1 - kb], B0, B1, B1, wave,
+                                                 kb ? wave - 2 : wave + 2, lane);
         const int krow = k0w + kb * 16 + c16;
-        if (krow >= Nk) continue;
+        if (krow >= Nk) return;
         if (G > 1) {
             // This query head's FP32 contributions; the group sum casts them.
             float* vp = dVp + poff + (size_t)krow * D;
@@ -873,7 +924,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
                 *reinterpret_cast<f32x4*>(vp + mb * 16 + 4 * g) = dv;
                 *reinterpret_cast<f32x4*>(kp + mb * 16 + 4 * g) = dk;
             }
-            continue;
+            return;
         }
         if (AB && dKacc != nullptr) {
             // the FP32 dK^acc for the correction pass, unscaled; dV final
@@ -892,7 +943,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
                 *reinterpret_cast<f32x4*>(kp + mb * 16 + 4 * g) = dk;
                 st_bf16x4(vrow + mb * 16 + 4 * g, dv[0], dv[1], dv[2], dv[3]);
             }
-            continue;
+            return;
         }
         uint16_t* vrow = dV + kvoff + (size_t)krow * D;
         uint16_t* krw = dK + kvoff + (size_t)krow * D;
@@ -909,7 +960,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
             st_bf16x4(vrow + mb * 16 + 4 * g, dv[0], dv[1], dv[2], dv[3]);
             st_bf16x4(krw + mb * 16 + 4 * g, dk[0], dk[1], dk[2], dk[3]);
         }
-    }
+    };
+    if (qh == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 1>{});
 }
 
 // Second key-major pass of the atomic GProj schedule (Algorithm 1's loop for
