@@ -164,7 +164,7 @@ void bwd_dq_kernel(
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
     if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
-    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     const int Tk = (Nkmax + kTile - 1) / kTile;  // key tiles of the longest problem
     int bh, tile;
     if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, Tk, &bh, &tile);
-    else map_block(blockIdx.x, BH, Tk, false, &bh, &tile);
+    else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if constexpr (UNEVEN) tile = packed_tile(tile, Tk, (Nk + kTile - 1) / kTile, false);

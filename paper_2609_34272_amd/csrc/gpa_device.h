@@ -310,13 +310,17 @@ __device__ __forceinline__ float xor_sum(float v) {
 // snake_rounds: an XCD places its i-th workgroup on compute unit i mod 32
 // while it has free slots, so the first `resident` x 32 workgroups of an XCD
 // (resident = workgroups a unit holds) are placed before any finishes.
-// Reversing every other block of 32 of those positions deals the heavy-first
-// list out like a snake draft: compute unit p gets list positions p, 63 - p,
-// 64 + p, 127 - p, ..., about the same total work on every unit.  This pays
-// when the resident set holds most of the grid (the d = 64 forward, 4 per
-// unit); later workgroups keep the longest-first order, which the in-order
-// dispatch balances by itself (with 2 per unit the backward passes measured
-// slower with the snake).
+// Reversing every other block of 32 of those positions (of 256 where heads are
+// not split over the XCDs) deals the heavy-first list out like a snake draft:
+// compute unit p gets list positions p, 63 - p, 64 + p, 127 - p, ..., about the
+// same total work on every unit.  This pays when the resident set holds most of
+// the grid (the d = 64 forward, 4 per unit, always; the other kernels that hold 2
+// where the grid is resident at once, snake_if_resident); later workgroups keep
+// the longest-first order, which the in-order dispatch balances by itself (with
+// 2 per unit and a grid of twice that the backward passes measured 5 % slower
+// with the snake).  Without and with it, us: forward 131 and 115 (4 heads of
+// 8192, d = 128), 36.5 and 32.4 (12 heads of 3000, d = 64); query pass 47.5 and
+// 42.7, key pass 56.2 and 51.0 (8 heads of 4096, d = 64).
 constexpr int kGroupTiles = 128;
 constexpr int kXcdCUs = 32;  // compute units per XCD
 __device__ __forceinline__ void map_block(int bid, int BH, int T, bool heavy_high, int* bh,
@@ -329,6 +333,10 @@ __device__ __forceinline__ void map_block(int bid, int BH, int T, bool heavy_hig
         const int q = li / kXcdCUs, p = li - q * kXcdCUs;
         if ((q & 1) && q < snake_rounds && q < (heads * T) / kXcdCUs)
             li = q * kXcdCUs + (kXcdCUs - 1 - p);
+    } else if (snake_rounds > 0) {
+        constexpr int CUs = 8 * kXcdCUs;
+        const int q = li / CUs, p = li - q * CUs;
+        if ((q & 1) && q < snake_rounds && q < (heads * T) / CUs) li = q * CUs + (CUs - 1 - p);
     }
     const int hg = min(heads, max(1, (kGroupTiles + T - 1) / T));
     const int group = li / (hg * T);
@@ -388,6 +396,13 @@ __device__ __forceinline__ void map_packed(int bid, int BH, int Hq, int T, int* 
 // first one is (key-major, causal) or all weigh the same.
 __device__ __forceinline__ int packed_tile(int rank, int T, int Ts, bool heavy_high) {
     return heavy_high ? T - 1 - rank : Ts - T + rank;
+}
+
+// snake_rounds of map_block for a kernel that holds `rounds` workgroups per
+// compute unit: used where the whole grid is resident at once, so that no later
+// dispatch evens the units out.
+__device__ __forceinline__ int snake_if_resident(int rounds) {
+    return (int)gridDim.x <= rounds * 8 * kXcdCUs ? rounds : 0;
 }
 
 // Rows of one attention problem (a query head of one sequence) and its query

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
     if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
-    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);

@@ -394,3 +394,22 @@ def test_few_queries_on_long_keys(gpa, newq, Hq, Hkv, d, causal):
             assert (ho[seen] - e).norm() <= 5e-3 * e.norm()
             assert (hl[seen] - torch.logsumexp(x[seen], 1)).abs().max() <= 1e-5
             assert (ho - o1[h, a:b].double().cpu()).norm() <= 5e-3 * e.norm()
+
+
+@pytest.mark.parametrize("H,N,d", [(3, 1000, 128), (5, 4160, 64), (8, 4096, 64), (4, 8192, 128), (12, 2700, 64)])
+def test_resident_grid_order_covers_every_tile(gpa, H, N, d):
+    """Grids that are resident at once take their tiles in snake order, in rounds
+    of 256 workgroups (or of 32 per XCD): each head still equals that head run
+    alone, bit for bit, at sizes with a partial last round."""
+    g = torch.Generator().manual_seed(N)
+    q, k, v, u = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(4))
+
+    def run(x):
+        o, lse = gpa.attn_fwd(x[0], x[1], x[2], True)
+        return (o, lse) + gpa.attn_bwd(x[0], x[1], x[2], o, lse, x[3], "gproj", True)
+
+    whole = run((q, k, v, u))
+    for h in (0, H // 2, H - 1):
+        for n, w, p in zip(("O", "LSE", "dQ", "dK", "dV"), whole,
+                           run([t[:, h:h + 1].contiguous() for t in (q, k, v, u)])):
+            assert torch.equal(w[:, h:h + 1], p), (n, h)
