@@ -163,12 +163,12 @@ void bwd_dq_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
-    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
+    if constexpr (UNEVEN) {
+        if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
+    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
-    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head
     const size_t kvoff = sr.kv0 * D;  // its key/value head
@@ -534,12 +534,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     const int Tq = (Nmax + kTile - 1) / kTile;   // query tiles of the longest problem
     const int Tk = (Nkmax + kTile - 1) / kTile;  // key tiles of the longest problem
     int bh, tile;
-    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, Tk, &bh, &tile);
-    else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
+    if constexpr (UNEVEN) {
+        if (!map_packed(blockIdx.x, BH, Hq, Nkmax, cu_k, total_k, false, &bh, &tile)) return;
+    } else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if constexpr (UNEVEN) tile = packed_tile(tile, Tk, (Nk + kTile - 1) / kTile, false);
-    if ((UNEVEN && tile < 0) || tile * kTile >= Nk) return;  // a shorter sequence has no such tile
+    if (tile * kTile >= Nk) return;  // a shorter sequence has no such tile
     const int T = (N + kTile - 1) / kTile;
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head: Q, dO, z
@@ -1379,6 +1379,7 @@ hipError_t launch_bwd_dq(const uint16_t* Q, const uint16_t* K, const uint16_t* V
     const int Nk = s.Nk > 0 ? s.Nk : s.N;
     dim3 grid((unsigned)(s.BH * T)), block(kThreads);
     const bool uneven = uneven_pack(s, s.total, s.N);
+    if (uneven) grid.x = packed_grid(s, s.total, s.N);
 #define GPA_DQ(DD, GP, WZ, NB)                                                                \
     launch_kernel(uneven ? bwd_dq_kernel<DD, GP, WZ, NB, true>                                \
                          : bwd_dq_kernel<DD, GP, WZ, NB, false>,                              \
@@ -1409,6 +1410,7 @@ hipError_t launch_bwd_dkdv(const uint16_t* Q, const uint16_t* K, const uint16_t*
     dim3 grid((unsigned)(s.BH * Tk)), block(kThreads);
     const bool gp = mode == 2;
     const bool uneven = uneven_pack(s, s.total_k, Nk);
+    if (uneven) grid.x = packed_grid(s, s.total_k, Nk);
 #define GPA_DKDV(DD, GP)                                                                      \
     launch_kernel(uneven ? bwd_dkdv_kernel<DD, GP, false, true>                               \
                          : bwd_dkdv_kernel<DD, GP, false, false>,                             \

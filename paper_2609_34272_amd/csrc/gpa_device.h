@@ -348,54 +348,109 @@ __device__ __forceinline__ void map_block(int bid, int BH, int T, bool heavy_hig
     *tile = heavy_high ? (T - 1 - rank) : rank;
 }
 
-// Workgroup -> (problem, rank) for packed sequences of unequal lengths, where
+// Workgroup -> (problem, tile) for packed sequences of unequal lengths, where
 // map_block's contiguous blocks of problems would give a whole long sequence to
 // one or two XCDs.  Query heads are split over the XCDs instead when Hq is a
 // multiple of 8 (XCD x takes heads [x Hq/8, (x+1) Hq/8) of every sequence, so
 // the XCDs carry equal work whatever the lengths and heads that share K and V
-// mostly share an L2); otherwise each rank rotates the problems by one, which
-// spreads every sequence over the XCDs.  Ranks count down from the longest
-// sequence's last tile (packed_tile), so the rank-major order is longest-first
-// across sequences; workgroups whose sequence has no such tile exit at once.
-// The problems are taken in groups of about kPackedTiles workgroups per XCD: a
-// group this size ends with a tail of a few per cent, and bounds the number of
-// heads whose K and V stream at the same time.  Measured, forward + query pass +
-// key pass: 12 sequences of 243 to 2431 tokens, 16 query heads on 4, d = 128:
-// 1453 us with map_block, 607 us with this (771 with groups of 128, 678 with one
-// group); 16 sequences of 500 to 7904 tokens, 32 heads on 8: 24.5 ms and 8.4 ms
-// (8.3 and 9.1); seven runs of 8192 and one of 8000, 32 heads: 25.0 ms and 25.1
-// ms (24.9 and 37.9: every head's K and V stream at once and miss in L2).
+// mostly share an L2); otherwise the heads rotate from one tile to the next,
+// which spreads every sequence over the XCDs.  Tiles are taken by the steps they
+// have left (a sequence with Ts tiles has one with each of Ts, Ts - 1, ..., 1
+// steps), most first across sequences: heavy_high: the last tile is the heaviest
+// (query-major, causal); otherwise the first one is (key-major, causal) or all
+// weigh the same.  The sequences are taken in groups of about kPackedTiles
+// workgroups per XCD: a group this size ends with a tail of a few per cent, and
+// bounds the number of heads whose K and V stream at the same time.
+//
+// With kPackedCompact sequences or fewer, lane s holds the tile count of sequence
+// s and a binary search over the steps left finds the k-th tile of the group's
+// order, so the grid needs about one workgroup per tile (packed_grid; those left
+// over, at most one per sequence and head, exit).  With more, every sequence has
+// as many places as the longest one, and workgroups whose sequence has no such
+// tile exit: 1000 exits cost a pass about 4 us.  Returns false where there is no
+// tile.
+//
+// Measured, forward + query pass + key pass: 12 sequences of 243 to 2431 tokens,
+// 16 query heads on 4, d = 128: 1453 us with map_block, 574 us with a place for
+// every tile of the longest sequence (groups of 128 workgroups 27 % slower, one
+// group 12 %), 552 us with this; the same on 4 heads 177 and 155; 16 sequences of
+// 500 to 7904 tokens, 32 heads on 8: 24.5, 8.08 and 7.83 ms; seven runs of 8192
+// and one of 8000, 32 heads: 25.0, 24.0 and 24.3 ms (37.9 in one group, where
+// every head's K and V stream at once and miss in L2).
 constexpr int kPackedTiles = 512;
-__device__ __forceinline__ void map_packed(int bid, int BH, int Hq, int T, int* bh, int* rank) {
-    const bool by_head = (Hq & 7) == 0;
-    const int per = by_head ? Hq >> 3 : 0;  // heads of a sequence on one XCD
-    const int probs = by_head ? BH >> 3 : BH;
-    const int li = by_head ? bid >> 3 : bid;
-    const int tiles = by_head ? kPackedTiles : 8 * kPackedTiles;
-    const int hg = min(probs, max(1, (tiles + T - 1) / T));
-    const int group = li / (hg * T);
-    const int first = group * hg;
-    const int gs = min(hg, probs - first);
-    const int within = li - first * T;
-    const int r = within / gs;
-    int p = within - r * gs;
-    if (by_head) {
-        p += first;
-        const int s = p / per;
-        *bh = s * Hq + (bid & 7) * per + (p - s * per);
-    } else {
-        *bh = first + (p + r) % gs;
-    }
-    *rank = r;
+constexpr int kPackedCompact = 64;
+
+// Sum over the 64 lanes, in every lane: rotations within the rows of 16 lanes,
+// then the row and half swaps of xor_sum.
+__device__ __forceinline__ int wave_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, true);  // row_ror:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, true);  // row_ror:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, true);  // row_ror:1
+    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = (int)(a[0] + a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
 }
 
-// Tile of a problem with Ts tiles at `rank` of T (the longest problem's count):
-// the tile with T - rank steps left when it is counted from the heavy end, so
-// every rank holds tiles of equal work; negative or >= Ts where there is none.
-// heavy_high: the last tile is the heaviest (query-major, causal); otherwise the
-// first one is (key-major, causal) or all weigh the same.
-__device__ __forceinline__ int packed_tile(int rank, int T, int Ts, bool heavy_high) {
-    return heavy_high ? T - 1 - rank : Ts - T + rank;
+__device__ __forceinline__ bool map_packed(int bid, int BH, int Hq, int Nmax, const int* cu,
+                                           int total, bool heavy_high, int* bh, int* tile) {
+    const int nseq = BH / Hq;
+    const int T = (Nmax + kTile - 1) / kTile;
+    const bool by_head = (Hq & 7) == 0;
+    const int per = by_head ? Hq >> 3 : Hq;  // heads of a place in one list
+    const int li = by_head ? bid >> 3 : bid;
+    const int tiles = by_head ? kPackedTiles : 8 * kPackedTiles;
+    const int gseq = (tiles + T * per - 1) / (T * per);  // sequences of a group
+    int k = li / per;                                    // place in the list of tiles
+    int h = li - k * per;
+    h = by_head ? (bid & 7) * per + h : (h + k) % per;
+    if (nseq > kPackedCompact) {
+        // places [group][steps left][sequence]
+        const int group = k / (gseq * T);
+        const int first = group * gseq;
+        const int gs = min(gseq, nseq - first);
+        const int within = k - first * T;
+        const int r = within / gs;
+        const int s = first + (within - r * gs);
+        const int x = min(max(cu[s], 0), total);
+        const int n = min(min(max(cu[s + 1], x), total) - x, Nmax);
+        const int Ts = (n + kTile - 1) / kTile;
+        *bh = s * Hq + h;
+        *tile = heavy_high ? T - 1 - r : Ts - T + r;
+        return T - r <= Ts;
+    }
+    const int lane = threadIdx.x & 63;
+    int Ts = 0;
+    if (lane < nseq) {
+        const int x = min(max(cu[lane], 0), total);
+        const int n = min(min(max(cu[lane + 1], x), total) - x, Nmax);
+        Ts = (n + kTile - 1) / kTile;
+    }
+    int t = 0, first = 0;
+    for (; first < nseq; first += gseq) {
+        t = lane >= first && lane < first + gseq ? Ts : 0;
+        const int sum = wave_sum(t);
+        if (k < sum) break;
+        k -= sum;
+    }
+    if (first >= nseq) return false;
+    // the most steps left, `lo`, that more than k tiles have or exceed
+    int lo = 1, hi = T;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (wave_sum(max(t - mid + 1, 0)) > k) lo = mid;
+        else hi = mid - 1;
+    }
+    k -= wave_sum(max(t - lo, 0));
+    const uint64_t with = __builtin_amdgcn_ballot_w64(t >= lo);
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(with >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)with, 0));
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(t >= lo && rank == k);
+    const int s = __builtin_ctzll(mine);
+    *bh = s * Hq + h;
+    *tile = heavy_high ? lo - 1 : __builtin_amdgcn_readlane(Ts, s) - lo;
+    return true;
 }
 
 // snake_rounds of map_block for a kernel that holds `rounds` workgroups per

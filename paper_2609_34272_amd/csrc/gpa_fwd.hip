@@ -56,12 +56,12 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
-    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
+    if constexpr (UNEVEN) {
+        if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
+    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
-    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head: Q, O
     const size_t kvoff = sr.kv0 * D;  // its key/value head
@@ -300,12 +300,12 @@ __global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    if constexpr (UNEVEN) map_packed(blockIdx.x, BH, Hq, T, &bh, &tile);
-    else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
+    if constexpr (UNEVEN) {
+        if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
+    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
-    if constexpr (UNEVEN) tile = packed_tile(tile, T, (N + kTile - 1) / kTile, causal != 0);
-    if ((UNEVEN && tile < 0) || tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if (tile * kTile >= N) return;  // a shorter sequence has no such tile
     const int off = Nk - N;  // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;
     const size_t kvoff = sr.kv0 * D;
@@ -718,6 +718,7 @@ hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, u
     // d = 64: one 16-query block per wave (measured faster); d = 128: two
     // blocks per wave, whose halved LDS reads matter more there.
     const bool uneven = uneven_pack(s, s.total, s.N);
+    if (uneven) grid.x = packed_grid(s, s.total, s.N);
 #define GPA_FWD(KERNEL, DD, FM, UN)                                                           \
     launch_kernel(KERNEL<DD, FM, UN>, grid, block, st, Q, K, V, O, LSE, s.BH, s.N, s.causal,      \
                   s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk > 0 ? s.Nk : s.N)

@@ -97,6 +97,17 @@ inline int few_splits(const Shape& s) {
     return n >= 2 || (s.G > 1 && s.G * s.N <= 64) ? (int)n : 0;
 }
 
+// Workgroups of the UNEVEN instantiations for one side: one place per tile (a
+// run's last tile may be partial) and head, or, with more sequences than the
+// kernels search among (kPackedCompact, 64), as many places for every sequence
+// as for the longest.
+inline unsigned packed_grid(const Shape& s, int total, int longest) {
+    const int64_t nseq = s.BH / s.Hq, T = (longest + 63) / 64;
+    int64_t places = nseq * T;
+    if (nseq <= 64 && total / 64 + nseq < places) places = total / 64 + nseq;
+    return (unsigned)(places * s.Hq);
+}
+
 // Kernel ids for timing (gpa_profile_*).
 enum KernelId {
     kKFwd = 0,

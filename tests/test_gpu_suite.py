@@ -320,14 +320,16 @@ def test_varlen_rejects_bad_arguments(gpa):
                             max_seqlen_k=case.total + 1)
 
 
-@pytest.mark.parametrize("Hq,Hkv,causal", [(8, 8, True), (16, 2, True), (16, 16, False), (3, 1, True),
-                                           (12, 4, False)])
-def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal):
+@pytest.mark.parametrize("Hq,Hkv,causal,reps", [
+    (8, 8, True, 5), (16, 2, True, 5), (16, 16, False, 5), (3, 1, True, 5), (12, 4, False, 5),
+    (8, 4, True, 9), (3, 3, False, 9), (16, 4, True, 0), (1, 1, True, 0)])
+def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal, reps):
     """Packs of unequal runs deal their heads over the XCDs when Hq is a
-    multiple of 8 and rotate the problems otherwise, in groups of sequences:
-    every problem's rows still equal a pack of that sequence alone, bit for bit
-    (more sequences than one group holds, empty and one-row runs among them)."""
-    lens = [1, 300, 64, 0, 129, 5, 190, 63] * 5 + [700, 65]
+    multiple of 8 and rotate them otherwise, in groups of sequences, and search
+    among 64 sequences at most (reps = 9 has 74): every problem's rows still
+    equal a pack of that sequence alone, bit for bit (more sequences than one
+    group holds, empty and one-row runs among them)."""
+    lens = [1, 300, 64, 0, 129, 5, 190, 63] * reps + [700, 65]
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     g = torch.Generator().manual_seed(Hq)
     total, d = int(cu[-1]), 64
@@ -345,7 +347,10 @@ def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal):
         return (o, lse) + gpa.attn_bwd_varlen(x[0], x[1], x[2], o, lse, x[3], c, m, "gproj", causal)
 
     whole = run(0, total)
-    for s in (0, 1, 2, 4, 5, 33, 38, 40, 41):
+    n = len(lens)
+    for s in sorted({0, 1, 2 % n, 4 % n, 5 % n, (n - 9) % n, (n - 4) % n, n - 2, n - 1}):
+        if lens[s] == 0:
+            continue
         a, b = int(cu[s]), int(cu[s + 1])
         for n, w, p in zip(("O", "LSE", "dQ", "dK", "dV"), whole, run(a, b)):
             assert torch.equal(w[:, a:b], p), (n, s)
