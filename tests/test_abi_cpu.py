@@ -187,3 +187,43 @@ def test_varlen_validation(lib):
     args = [P + i * 0x10000000 for i in range(9)]
     assert lib.gpa_attn_bwd_varlen(*args, P + 0x90000000, None, 3, 300, 300, 4, 2, 128, 128, 64,
                                    1, 0.125, 2, P + 0xA0000000, 16, None) == 3
+
+
+def test_few_query_forward_workspace_and_validation(lib):
+    """Which packed shapes take the split forward, the bytes it asks for, and its
+    host-side checks."""
+    f = lib.gpa_attn_fwd_varlen_workspace_bytes
+    few = (8, 32, 30000, 16, 4, 4, 5115, 128)  # 8 sequences of 4 queries
+    n = f(*few)
+    splits = 5115 // 256 + 1                   # four key tiles or more each
+    assert n == splits * 16 * 32 * (128 + 2) * 4
+    # the ordinary forward: short keys, many queries, too few keys per query,
+    # enough workgroups without a group to share
+    assert f(8, 32, 8000, 16, 4, 4, 2047, 128) == 0
+    assert f(8, 1032, 30000, 16, 4, 129, 5115, 128) == 0
+    assert f(4, 512, 8000, 16, 4, 128, 2048 - 1, 128) == 0
+    assert f(2, 600, 6000, 16, 4, 300, 2400, 64) == 0
+    assert f(64, 64, 128000, 32, 32, 1, 2048, 64) == 0
+    # a group's rows in one tile: one pass over K and V even without splits
+    assert f(128, 1024, 256000, 32, 8, 8, 2048, 128) == 1024 * 32 * (128 + 2) * 4
+    # no more than kFewTarget workgroups' worth of rows beyond the rows themselves
+    for nseq, q in ((1, 1), (3, 128), (400, 100)):
+        rows = nseq * q * 16
+        assert f(nseq, nseq * q, nseq * 4096, 16, 16, q, 4096, 64) <= (64 * 1024 + 2 * rows) * 66 * 4 + 512
+    # invalid shapes
+    assert f(0, 32, 30000, 16, 4, 4, 5115, 128) == 0
+    assert f(8, 32, 30000, 16, 5, 4, 5115, 128) == 0
+    assert f(8, 32, 30000, 16, 4, 4, 5115, 96) == 0
+
+    P = FAKE
+
+    def call(ws=FAKE + 0x90000000, ws_bytes=n, O=FAKE + 0x30000000, cu=FAKE + 0x50000000):
+        return lib.gpa_attn_fwd_varlen_ws(P, P + 0x10000000, P + 0x20000000, O, P + 0x40000000, cu,
+                                          P + 0x60000000, *few[:1], *few[1:], 1, 0.1, ws, ws_bytes,
+                                          None)
+    assert call(ws=None) == 3 and call(ws_bytes=n - 1) == 3
+    assert call(ws=FAKE + 0x90000010) == 3                # not 256-byte aligned
+    assert call(ws=FAKE) == 1                             # overlaps Q
+    assert call(O=FAKE + 0x90000000) == 1                 # O overlaps the workspace
+    assert call(ws=FAKE + 0x50000000) == 1                # overlaps the offsets
+    assert call(cu=None) == 1 and call(O=None) == 1
