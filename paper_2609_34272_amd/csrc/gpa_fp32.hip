@@ -20,8 +20,8 @@
 // bias 0 to 64; LSE 3.0e-8 to 4.3e-8 (3.1e-8 to 4.9e-8).  What bounds the
 // kernels now is the vector ALU (the split is 5.5 instructions per pair and FP32
 // factor, of 11 to 20): forward / query pass / key pass 369 / 537 / 659 us on the
-// FP32 matrix cores, 85 / 96 / 136 us here (16 heads of 4096 causal tokens, d =
-// 64; 1552 and 316 us in all).
+// FP32 matrix cores, 85 / 90 / 134 us here (16 heads of 4096 causal tokens, d =
+// 64; 1552 and 307 us in all).
 //
 // MFMA layouts as in the BF16 kernels (16x16x32, wave64): lane (c16 = lane & 15,
 // g = lane >> 4) supplies 8 values along k of row (A) or column (B) c16; the
@@ -33,7 +33,11 @@
 // Work split: a workgroup has 4 waves and owns 64 rows (queries in the
 // forward and the query-major pass, keys in the key-major pass), 16 per wave;
 // it streams 64-row tiles of the other side through a double-buffered LDS
-// ring filled with the LDS DMA load.
+// ring filled with the LDS DMA load.  At d = 64 a unit holds 4 workgroups of the
+// forward and the query pass and 3 of the key pass, so those rounds are dealt
+// out in snake order: 92 / 101 / 143 us without it and 89 / 94 / 140 with it (16
+// heads of 4096, one box), 357 / 387 / 539 and 316 / 346 / 534 (16 of 8192); no
+// difference at d = 128.
 #include "gpa_device.h"
 #include "gpa_launch.h"
 
@@ -133,7 +137,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 4 : 0);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile);
+    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 4 : 0);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -380,7 +384,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
     __shared__ __attribute__((aligned(16))) float ST1[kF32Stat];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, false, &bh, &tile);
+    map_block(blockIdx.x, BH, T, false, &bh, &tile, D == 64 ? 3 : 0);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
