@@ -36,7 +36,7 @@
 // ring filled with the LDS DMA load.  At d = 64 a unit holds 4 workgroups of the
 // forward and the query pass and 3 of the key pass, so those rounds are dealt
 // out in snake order: 92 / 101 / 143 us without it and 89 / 94 / 140 with it (16
-// heads of 4096, one box), 357 / 387 / 539 and 316 / 346 / 534 (16 of 8192); no
+// heads of 4096), 357 / 387 / 539 and 316 / 346 / 534 (16 of 8192); no
 // difference at d = 128.
 #include "gpa_device.h"
 #include "gpa_launch.h"
