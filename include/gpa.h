@@ -295,15 +295,22 @@ gpa_status gpa_attn_fwd_varlen(const uint16_t* Q, const uint16_t* K, const uint1
                                void* stream);
 
 /*
- * gpa_attn_fwd_varlen with a workspace, for few queries on long key runs (new
- * tokens against their past): the keys of such a call are split over several
- * workgroups and the heads of a group share one pass over K and V.  Whether a
- * shape is one is decided from its sizes: gpa_attn_fwd_varlen_workspace_bytes
- * returns the bytes it needs, or 0 where the call is gpa_attn_fwd_varlen itself
- * (which it then is, bit for bit, and workspace may be NULL).  Same arguments,
- * arithmetic per (query, key) and errors otherwise; the FP32 sums are taken in
- * another order.  workspace: at least that many bytes, 256-byte aligned, not
- * overlapping any other buffer; its contents do not matter.
+ * gpa_attn_fwd_varlen for packs with few queries on long key runs among their
+ * sequences (new tokens against their past).  Such a sequence (nq <= 128, nk >=
+ * 512, and (Hq/Hkv) nq <= 64 or <= nk/16) has its keys split over several
+ * workgroups, and the heads of a group share one pass over K and V.  Arithmetic per
+ * (query, key) is the same; its FP32 sums are taken per split (4 key tiles of 64 per
+ * 64 rows or more, 8 splits at most) and then over the splits, so its O and LSE are
+ * not bit for bit those of gpa_attn_fwd_varlen.  They depend on the sequence's own
+ * rows and sizes alone, not on the sequences beside it.  Every other sequence's
+ * (nq == nk among them) are gpa_attn_fwd_varlen's, bit for bit.
+ *
+ * workspace: at least gpa_attn_fwd_varlen_workspace_bytes(...) bytes, 256-byte
+ * aligned, not overlapping any other buffer; its contents do not matter.  0 bytes
+ * (max_seqlen_k < 512), or one array of offsets for both sides: no sequence is such
+ * a one, and the call is gpa_attn_fwd_varlen.  workspace NULL with workspace_bytes 0:
+ * one workgroup takes a sequence's splits in turn, slower, with the same results bit
+ * for bit.  Arguments and errors otherwise as above.
  */
 size_t gpa_attn_fwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_t total_k,
                                            int64_t Hq, int64_t Hkv, int64_t max_seqlen_q,

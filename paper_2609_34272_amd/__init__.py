@@ -366,8 +366,10 @@ def attn_fwd_varlen(q, k, v, cu_seqlens, max_seqlen: int, causal: bool = True, s
     GPU (sequence s = queries cu[s] .. cu[s+1]-1); max_seqlen: the longest
     query run.  cu_seqlens_k / max_seqlen_k give the key side (default: the
     same as the queries); with causal the diagonal is aligned at the last
-    query and key, and a query that sees no key gets O = 0, LSE = +inf.  Few
-    queries on long key runs go through gpa_attn_fwd_varlen_ws.
+    query and key, and a query that sees no key gets O = 0, LSE = +inf.  A
+    sequence's results do not depend on the sequences beside it: with nq == nk
+    they are attn_fwd's bit for bit; with few queries on many keys the keys are
+    split (gpa_attn_fwd_varlen_ws).
     Returns O (bf16 [Hq, total_q, d]) and LSE (float32 [Hq, total_q])."""
     pk = _Packed(q, k, cu_seqlens, max_seqlen, cu_seqlens_k, max_seqlen_k)
     _need(q, "q", (pk.Hq, pk.total_q, pk.d), torch.bfloat16)
@@ -375,23 +377,25 @@ def attn_fwd_varlen(q, k, v, cu_seqlens, max_seqlen: int, causal: bool = True, s
         _need(t, n, (pk.Hkv, pk.total_k, pk.d), torch.bfloat16)
     o = torch.empty_like(q)
     lse = torch.empty((pk.Hq, pk.total_q), dtype=torch.float32, device=q.device)
-    # few queries on long key runs: the keys are split, in a workspace (the
-    # ordinary forward, which needs none, where it cannot be had)
-    nbytes = 0 if pk.max_k < 2048 else int(lib().gpa_attn_fwd_varlen_workspace_bytes(
+    if pk.cu_k is pk.cu_q:
+        _check(lib().gpa_attn_fwd_varlen(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                         lse.data_ptr(), *pk.offsets(), int(bool(causal)),
+                                         _scale(pk.d, scale), _stream(q)))
+        return o, lse
+    # sequences with few queries on long key runs: their keys are split, in a
+    # workspace (where it cannot be had, one split after the other)
+    nbytes = int(lib().gpa_attn_fwd_varlen_workspace_bytes(
         pk.nseq, pk.total_q, pk.total_k, pk.Hq, pk.Hkv, pk.max_q, pk.max_k, pk.d))
+    ws = None
     if nbytes:
         try:
             ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
         except torch.OutOfMemoryError:
             nbytes = 0
-    if nbytes:
-        _check(lib().gpa_attn_fwd_varlen_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                            lse.data_ptr(), *pk.offsets(), int(bool(causal)),
-                                            _scale(pk.d, scale), ws.data_ptr(), nbytes, _stream(q)))
-        return o, lse
-    _check(lib().gpa_attn_fwd_varlen(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                     lse.data_ptr(), *pk.offsets(), int(bool(causal)),
-                                     _scale(pk.d, scale), _stream(q)))
+    _check(lib().gpa_attn_fwd_varlen_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                        lse.data_ptr(), *pk.offsets(), int(bool(causal)),
+                                        _scale(pk.d, scale), None if ws is None else ws.data_ptr(),
+                                        nbytes, _stream(q)))
     return o, lse
 
 

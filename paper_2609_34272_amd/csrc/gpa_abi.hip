@@ -339,13 +339,14 @@ BwdLayout varlen_layout(const Varlen& v, int mode) {
     return bwd_layout_rows((size_t)v.Hq * v.total_q, (size_t)v.Hq * v.total_k,
                            (size_t)v.nseq * v.Hq, v.max_q, v.d, mode, v.Hq > v.Hkv);
 }
-// Workspace of the forward for few queries on long key runs: per split the FP32
-// O accumulators over the query-head rows, then row maximum and row sum.
+// Workspace of the forward that splits the keys of sequences with few queries: the
+// FP32 O accumulators of the state rows, then their row maxima and sums.
 struct FewLayout {
     size_t oacc, ml, total;
 };
-FewLayout few_layout(const Varlen& v, int splits) {
-    const size_t rows = (size_t)splits * v.Hq * v.total_q;
+FewLayout few_layout(const Varlen& v) {
+    const size_t rows =
+        (size_t)v.Hkv * gpa::few_base(v.nseq, v.total_q, v.total_k, v.Hq / v.Hkv);
     FewLayout L;
     L.oacc = 0;
     L.ml = round_up(rows * (size_t)v.d * sizeof(float));
@@ -615,10 +616,9 @@ size_t gpa_attn_fwd_varlen_workspace_bytes(int64_t nseq, int64_t total_q, int64_
     if (gpa_attn_bwd_varlen_workspace_bytes(nseq, total_q, total_k, Hq, Hkv, max_seqlen_q,
                                             max_seqlen_k, d, 0) == 0)
         return 0;
-    static const int32_t some = 0;  // marks the shape as packed; never read
-    const Varlen v{&some, &some, nseq, total_q, total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d};
-    const int n = gpa::few_splits(varlen_shape(v, 1, 1.f));
-    return n ? few_layout(v, n).total : 0;
+    static const int32_t some[2] = {};  // two sets of offsets; never read
+    const Varlen v{some, some + 1, nseq, total_q, total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d};
+    return gpa::may_have_few(varlen_shape(v, 1, 1.f)) ? few_layout(v).total : 0;
 }
 
 gpa_status gpa_attn_fwd_varlen_ws(const uint16_t* Q, const uint16_t* K, const uint16_t* V,
@@ -632,33 +632,34 @@ gpa_status gpa_attn_fwd_varlen_ws(const uint16_t* Q, const uint16_t* K, const ui
     gpa_status s = check_varlen(v, scale);
     if (s != GPA_OK) return s;
     const gpa::Shape sh = varlen_shape(v, causal, scale);
-    const int n = gpa::few_splits(sh);
-    if (n == 0)
+    if (!gpa::may_have_few(sh))
         return gpa_attn_fwd_varlen(Q, K, V, O, LSE, cu_seqlens_q, cu_seqlens_k, nseq, total_q,
                                    total_k, Hq, Hkv, max_seqlen_q, max_seqlen_k, d, causal, scale,
                                    stream);
-    const FewLayout L = few_layout(v, n);
-    if (!workspace || workspace_bytes < L.total)
+    const bool walk = !workspace && workspace_bytes == 0;
+    const FewLayout L = few_layout(v);
+    if (!walk && (!workspace || workspace_bytes < L.total))
         return fail(GPA_EWORKSPACE, "workspace %p of %zu bytes; %zu needed", workspace,
                     workspace_bytes, L.total);
     if ((uintptr_t)workspace % kAlign)
         return fail(GPA_EWORKSPACE, "workspace is not %zu-byte aligned", kAlign);
     const size_t tq = (size_t)Hq * total_q * d * 2, tkv = (size_t)Hkv * total_k * d * 2;
     const size_t lb = (size_t)Hq * total_q * 4;
-    const std::vector<Buf> outs = {{O, tq, "O"}, {LSE, lb, "LSE"}, {workspace, L.total, "workspace"}};
+    std::vector<Buf> outs = {{O, tq, "O"}, {LSE, lb, "LSE"}};
+    if (!walk) outs.push_back({workspace, L.total, "workspace"});
     s = check_ptrs({{Q, tq, "Q"}, {K, tkv, "K"}, {V, tkv, "V"}}, outs);
     if (s != GPA_OK) return s;
     if ((s = check_cu_overlap(v, outs)) != GPA_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    float* oacc = (float*)(ws + L.oacc);
-    float* ml = (float*)(ws + L.ml);
+    float* oacc = walk ? nullptr : (float*)(ws + L.oacc);
+    float* ml = walk ? nullptr : (float*)(ws + L.ml);
     s = launched(timed(gpa::kKFwdFew,
-                       [&] { return gpa::launch_fwd_few(Q, K, V, oacc, ml, n, sh, st); }),
+                       [&] { return gpa::launch_fwd_few(Q, K, V, O, LSE, oacc, ml, sh, st); }),
                  "fwd_few");
-    if (s != GPA_OK) return s;
+    if (s != GPA_OK || walk) return s;
     return launched(timed(gpa::kKFwdFewMerge,
-                          [&] { return gpa::launch_fwd_few_merge(oacc, ml, O, LSE, n, sh, st); }),
+                          [&] { return gpa::launch_fwd_few_merge(oacc, ml, O, LSE, sh, st); }),
                     "fwd_few_merge");
 }
 

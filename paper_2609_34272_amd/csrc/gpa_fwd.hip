@@ -18,6 +18,7 @@
 #include "gpa_device.h"
 #include "gpa_launch.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace gpa {
@@ -40,12 +41,243 @@ __device__ __forceinline__ float exp_arg(float x, float m, float c) {
     }
 }
 
-template <int D, bool FMA, bool UNEVEN>
-__global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
+// How a forward kernel takes the packed sequences that few_sequence (gpa_launch.h)
+// names: not apart from the others, by splits that leave their states in a
+// workspace, or by splits one after the other.
+enum class Few { kNone, kSplit, kWalk };
+struct FewArgs {
+    float* Oacc = nullptr;  // states: FP32 O^T accumulators [Hkv, rows, D],
+    float* ML = nullptr;    // row maxima and sums [Hkv, rows, 2]
+    int64_t rows = 0;       // state rows of a key/value head
+    int blocks = 0;         // workgroups that take them, before the others
+    int places = 0;         // (row tile, split) places of a (sequence, key/value head)
+    uint32_t items = 0;     // places in all
+};
+
+// Weights of a row's state (maximum m) and of the next split's (maximum mi) under
+// their common maximum, by the rescale rule that the forward uses between tiles.
+__device__ __forceinline__ void few_weights(float& m, float mi, float c, float& w, float& wi) {
+    const float mn = fmaxf(m, mi);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;
+    w = fexp2((m - ms) * c);
+    wi = fexp2((mi - ms) * c);
+    m = mn;
+}
+
+// Few queries against long key runs.  A workgroup of the kernels below would fill
+// a few of its 64 query rows and walk every key tile alone, and each query head
+// would read its group's K and V again.  Here the rows of a (sequence, key/value
+// head) are all G heads' queries (row r: head r / nq, query r % nq), so K and V are
+// read once per row tile, and the key tiles are split (few_chunk).  Per (query, key)
+// the arithmetic is fwd_sbs_q16_kernel's; every split has an unnormalised state (O^T
+// accumulator, row maximum, row sum; FP32) of its own, and the states of a row are
+// taken together in split order, by fwd_few_merge_kernel or (kWalk) right here.
+// These workgroups run in the launch of the pack's other sequences, in front of
+// them: a launch of their own would leave the chip to short sequences that take as
+// long.  What bounds it: the latency of each split's few tiles, then HBM.  8
+// sequences of 4 queries on 406 to 5115 keys, 16 heads on 4, d = 128 (47 MB of K and
+// V): 68 us in the ordinary forward, 14.8 us here and 4.3 us for the merge; 24 of 1
+// on 1292 to 8192 keys, 32 heads on 8 (466 MB): 270 us, 84 and 4.6 us (5.5 TB/s).
+template <int D, Few FEW>
+__device__ __forceinline__ void few_rows(
+    uint16_t (&KV0)[2][kTile * D], uint16_t (&KV1)[2][kTile * D], int bid,
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, uint16_t* __restrict__ O, float* __restrict__ LSE, int Nmax,
+    int causal, float scale, int G, const int* __restrict__ cu, int Hq, int total,
+    const int* __restrict__ cu_k, int total_k, int Nkmax, const FewArgs& few) {
+    constexpr int MB = D / 16;
+    constexpr int KC = D / 32;
+    const int Hkv = Hq / G;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c16 = lane & 15;
+    const float c = scale * kLog2e;
+    TileDma<D> dma;
+    dma.init(lane, wave);
+
+    // items [sequence][key/value head][place]
+    for (uint32_t item = bid; item < few.items; item += few.blocks) {
+        const int prob = (int)(item / few.places);
+        const int place = (int)(item - (uint32_t)prob * few.places);
+        const int seq = prob / Hkv, kvh = prob - seq * Hkv;
+        const SeqRows sr = seq_rows(cu, cu_k, seq * Hq + kvh * G, Nmax, Nkmax, G, Hq, total, total_k);
+        const int N = sr.nq, Nk = sr.nk;
+        if (N == 0 || !few_sequence(N, Nk, G)) continue;
+        const int rows = G * N;
+        const int RT = (rows + kTile - 1) / kTile, tiles = (Nk + kTile - 1) / kTile;
+        const int chunk = few_chunk(RT, tiles);
+        const int S = (tiles + chunk - 1) / chunk;
+        // Each problem's places begin elsewhere, so that problems that fill few of them
+        // are spread over the XCDs all the same.
+        const int w = (int)(((uint32_t)place + 3u * (uint32_t)prob) % (uint32_t)few.places);
+        const int rt = FEW == Few::kWalk ? w : w / S, first = FEW == Few::kWalk ? 0 : w % S;
+        if (rt >= RT) continue;
+        const int last = FEW == Few::kWalk ? S : first + 1;
+        const int off = Nk - N;
+        const size_t kvoff = sr.kv0 * D;
+        const int r = rt * kTile + 16 * wave + c16;         // this lane's row
+        const bool active = rt * kTile + 16 * wave < rows;  // the wave has a row
+        const int hg = r / N, qi = r - hg * N;       // its head in the group and query
+        const size_t qrow = sr.q0 + (size_t)hg * total + qi;  // its row of Q, O and LSE
+
+        // the first tile's loads go out before the operands'
+        auto fill = [&](int kt, uint16_t (&KV)[2][kTile * D]) {
+            dma.load(K + kvoff, KV[0], kt * kTile, Nk);
+            dma.load(V + kvoff, KV[1], kt * kTile, Nk);
+        };
+        wait_vm_lgkm0<0>();
+        fill(first * chunk, KV0);
+        bf16x8 qf[KC];
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+            u32x4 w = {0u, 0u, 0u, 0u};
+            if (r < rows) w = *reinterpret_cast<const u32x4*>(Q + qrow * D + kc * 32 + 8 * g);
+            qf[kc] = __builtin_bit_cast(bf16x8, w);
+        }
+        // the first tile that needs masks: every query sees the keys up to the
+        // first query's last one
+        const int nplain = min(causal ? max(floor_div(off + 1, kTile), 0) : Nk / kTile, Nk / kTile);
+
+        float mrow = -INFINITY, lrow = 0.f;  // kWalk: the row's state so far
+        f32x4 orow[MB];
+        if constexpr (FEW == Few::kWalk)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) orow[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+        for (int split = first; split < last; ++split) {
+            float mrun = -INFINITY, lrun = 0.f;
+            f32x4 acc[MB];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int kt0 = split * chunk, kt1 = min(kt0 + chunk, tiles);
+
+            if (split > first) fill(kt0, KV0);
+            wait_vm_lgkm0<0>();
+            __syncthreads();
+
+            auto compute = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc) {
+                constexpr bool MASK = decltype(masked)::value;
+                f32x4 s[4];
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kc = 0; kc < KC; ++kc)
+                        s[kb] = mfma_16x16x32(
+                            ld_b128(Kc + tile_off<D>(kb * 16 + c16, kc * 32 + 8 * g)), qf[kc], s[kb]);
+                }
+                if constexpr (MASK) {
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int key = kt * kTile + kb * 16 + 4 * g + i;
+                            const bool ok = key < Nk && (!causal || key <= qi + off);
+                            s[kb][i] = ok ? s[kb][i] : -INFINITY;
+                        }
+                }
+                float mx = s[0][0];
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kb][i]);
+                mx = xor_max(mx);
+                const float mnew = fmaxf(mrun, mx);
+                const float ms = (mnew == -INFINITY) ? 0.f : mnew;
+                if (__builtin_amdgcn_ballot_w64(mnew != mrun) != 0) {
+                    const float corr = fexp2((mrun - ms) * c);
+                    lrun *= corr;
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
+                }
+                bf16x8 pf[2];
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float z = fexp2(exp_arg<false>(s[kb][i], ms, c));
+                        lrun += z;
+                        pf[kb >> 1][(kb & 1) * 4 + i] = to_bf16(z);
+                    }
+                mrun = mnew;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[mb] = mfma_16x16x32(ld_tr_operand<D>(Vc, 32 * j, mb * 16, c16, g), pf[j],
+                                                acc[mb]);
+            };
+            auto step = [&](int kt, const uint16_t (&KV)[2][kTile * D],
+                            uint16_t (&next)[2][kTile * D]) {
+                if (kt + 1 < kt1) fill(kt + 1, next);
+                __builtin_amdgcn_sched_barrier(0);
+                if (active) {
+                    if (kt < nplain) compute(std::false_type{}, kt, KV[0], KV[1]);
+                    else compute(std::true_type{}, kt, KV[0], KV[1]);
+                }
+                wait_vm_lgkm0<0>();
+                __syncthreads();
+            };
+            for (int kt = kt0; kt < kt1; kt += 2) {
+                step(kt, KV0, KV1);
+                if (kt + 1 < kt1) step(kt + 1, KV1, KV0);
+            }
+
+            const float ltot = xor_sum(lrun);
+            if constexpr (FEW == Few::kWalk) {
+                // l = 0: the split saw none of the row's keys (on the bits, as in
+                // the kernels below), and its accumulator may hold anything
+                if (__float_as_uint(ltot) != 0u) {
+                    float w, wi;
+                    few_weights(mrow, mrun, c, w, wi);
+                    lrow = __builtin_fmaf(ltot, wi, lrow * w);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            orow[mb][i] = __builtin_fmaf(acc[mb][i], wi, orow[mb][i] * w);
+                }
+            } else if (r < rows) {
+                const size_t p = (size_t)kvh * few.rows +
+                                 few_base(seq, sr.q0 - (size_t)kvh * G * total,
+                                          sr.kv0 - (size_t)kvh * total_k, G) +
+                                 (size_t)split * rows + r;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    *reinterpret_cast<f32x4*>(few.Oacc + p * D + mb * 16 + 4 * g) = acc[mb];
+                if (g == 0) {
+                    few.ML[2 * p] = mrun;
+                    few.ML[2 * p + 1] = ltot;
+                }
+            }
+        }
+        if constexpr (FEW == Few::kWalk) {
+            if (r < rows) {
+                const bool empty = __float_as_uint(lrow) == 0u;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    float v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = empty ? 0.f : orow[mb][i] / lrow;
+                    st_bf16x4(O + qrow * D + mb * 16 + 4 * g, v[0], v[1], v[2], v[3]);
+                }
+                if (g == 0) {
+#pragma clang fp contract(off)
+                    const float lse = scale * mrow + logf(lrow);
+                    LSE[qrow] = empty ? INFINITY : lse;
+                }
+            }
+        }
+    }
+}
+
+template <int D, bool FMA, bool UNEVEN, Few FEW>
+__global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 1 : GPA_FWD_OCC) void fwd_sbs_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, float* __restrict__ LSE,
     int BH, int Nmax, int causal, float scale, int G, const int* __restrict__ cu, int Hq,
-    int total, const int* __restrict__ cu_k, int total_k, int Nkmax) {
+    int total, const int* __restrict__ cu_k, int total_k, int Nkmax, FewArgs few) {
     constexpr int MB = D / 16;
     constexpr int KC = D / 32;
     constexpr int PER_NB = MB * 4 + 2;  // acc, m, l of one query block
@@ -54,14 +286,25 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
 
+    int bid = blockIdx.x;
+    if constexpr (FEW != Few::kNone) {
+        if (bid < few.blocks) {
+            few_rows<D, FEW>(KV0, KV1, bid, Q, K, V, O, LSE, Nmax, causal, scale, G, cu, Hq, total,
+                             cu_k, total_k, Nkmax, few);
+            return;
+        }
+        bid -= few.blocks;
+    }
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
     if constexpr (UNEVEN) {
-        if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
+        if (!map_packed(bid, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
+    } else map_block(bid, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if constexpr (FEW != Few::kNone)
+        if (few_sequence(N, Nk, G)) return;  // taken by few_rows
     const int off = Nk - N;           // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;    // query head: Q, O
     const size_t kvoff = sr.kv0 * D;  // its key/value head
@@ -287,25 +530,36 @@ __global__ __launch_bounds__(kThreads, GPA_FWD_OCC) void fwd_sbs_kernel(
 // partial states is needed; the price is that every K and V fragment read from
 // LDS feeds one MFMA instead of two.  Fewer registers per wave allow more
 // waves per SIMD.  The arithmetic per (query, key) is that of fwd_sbs_kernel.
-template <int D, bool FMA, bool UNEVEN>
-__global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
+template <int D, bool FMA, bool UNEVEN, Few FEW>
+__global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 2 : GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, float* __restrict__ LSE,
     int BH, int Nmax, int causal, float scale, int G, const int* __restrict__ cu, int Hq,
-    int total, const int* __restrict__ cu_k, int total_k, int Nkmax) {
+    int total, const int* __restrict__ cu_k, int total_k, int Nkmax, FewArgs few) {
     constexpr int MB = D / 16;
     constexpr int KC = D / 32;
     __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
 
+    int bid = blockIdx.x;
+    if constexpr (FEW != Few::kNone) {
+        if (bid < few.blocks) {
+            few_rows<D, FEW>(KV0, KV1, bid, Q, K, V, O, LSE, Nmax, causal, scale, G, cu, Hq, total,
+                             cu_k, total_k, Nkmax, few);
+            return;
+        }
+        bid -= few.blocks;
+    }
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
     if constexpr (UNEVEN) {
-        if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
+        if (!map_packed(bid, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
+    } else map_block(bid, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile
+    if constexpr (FEW != Few::kNone)
+        if (few_sequence(N, Nk, G)) return;  // taken by few_rows
     const int off = Nk - N;  // causal: query i sees key j iff j <= i + off
     const size_t hoff = sr.q0 * D;
     const size_t kvoff = sr.kv0 * D;
@@ -446,292 +700,184 @@ __global__ __launch_bounds__(kThreads, GPA_FWD16_OCC) void fwd_sbs_q16_kernel(
     }
 }
 
-// Few queries against long key runs (packed sequences; the rule and the number
-// of splits are few_splits' in gpa_launch.h).  A workgroup of the kernels above
-// would fill a few of its 64 query rows and walk every key tile alone, and each
-// query head would read its group's K and V again.  Here the rows of a
-// (sequence, key/value head) are all G heads' queries (row r: head r / nq, query
-// r % nq), so K and V are read once per group, and the key tiles are split over
-// S workgroups, each leaving its unnormalised state (O^T accumulator, row
-// maximum, row sum; FP32) in the workspace for fwd_few_merge_kernel.  Per
-// (query, key) the arithmetic is fwd_sbs_q16_kernel's, and the states merge by
-// the rescale rule it uses between tiles.  What bounds it: the latency of each
-// split's few tiles, then HBM; 8 sequences of 4 queries on 406 to 5115 keys, 16
-// heads on 4, d = 128 (47 MB of K and V): 68.7 us before, 17 us with the merge.
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void fwd_few_kernel(
-    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-    const uint16_t* __restrict__ V, float* __restrict__ Oacc, float* __restrict__ ML, int Nmax,
-    int causal, float scale, int G, const int* __restrict__ cu, int Hq, int total,
-    const int* __restrict__ cu_k, int total_k, int Nkmax, int S) {
-    constexpr int MB = D / 16;
-    constexpr int KC = D / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t KV0[2][kTile * D];
-    __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
-
-    // blockIdx: split fastest, then row tile, then (sequence, key/value head)
-    const int RT = (G * Nmax + kTile - 1) / kTile;
-    const int split = blockIdx.x % S;
-    const int rest = blockIdx.x / S;
-    const int rt = rest % RT, prob = rest / RT;
-    const int Hkv = Hq / G;
-    const int seq = prob / Hkv, kvh = prob - seq * Hkv;
-    const SeqRows sr = seq_rows(cu, cu_k, seq * Hq + kvh * G, Nmax, Nkmax, G, Hq, total, total_k);
-    const int N = sr.nq, Nk = sr.nk;
-    const int rows = G * N;
-    if (rt * kTile >= rows) return;
-    const int off = Nk - N;
-    const size_t kvoff = sr.kv0 * D;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c16 = lane & 15;
-    const int r = rt * kTile + 16 * wave + c16;  // this lane's row
-    const bool active = rt * kTile + 16 * wave < rows;  // the wave has a row
-    const int hg = r / N, qi = r - hg * N;       // its head in the group and query
-    const size_t qrow = sr.q0 + (size_t)hg * total + qi;  // its row of Q, O and LSE
-
-    bf16x8 qf[KC];
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-        u32x4 w = {0u, 0u, 0u, 0u};
-        if (r < rows) w = *reinterpret_cast<const u32x4*>(Q + qrow * D + kc * 32 + 8 * g);
-        qf[kc] = __builtin_bit_cast(bf16x8, w);
-    }
-    const float c = scale * kLog2e;
-    float mrun = -INFINITY, lrun = 0.f;
-    f32x4 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // Key tiles of the sequence, of this split, and the first that needs masks
-    // (every query sees the keys up to the first query's last one).
-    const int tiles = (Nk + kTile - 1) / kTile;
-    const int chunk = (tiles + S - 1) / S;
-    const int kt0 = min(split * chunk, tiles), kt1 = min(kt0 + chunk, tiles);
-    const int nplain = min(causal ? max(floor_div(off + 1, kTile), 0) : Nk / kTile, Nk / kTile);
-
-    TileDma<D> dma;
-    dma.init(lane, wave);
-    wait_vm_lgkm0<0>();
-    if (kt0 < kt1) {
-        dma.load(K + kvoff, KV0[0], kt0 * kTile, Nk);
-        dma.load(V + kvoff, KV0[1], kt0 * kTile, Nk);
-    }
-    wait_vm_lgkm0<0>();
-    __builtin_amdgcn_s_barrier();
-
-    auto compute = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc) {
-        constexpr bool MASK = decltype(masked)::value;
-        f32x4 s[4];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kc = 0; kc < KC; ++kc)
-                s[kb] = mfma_16x16x32(ld_b128(Kc + tile_off<D>(kb * 16 + c16, kc * 32 + 8 * g)),
-                                      qf[kc], s[kb]);
-        }
-        if constexpr (MASK) {
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int key = kt * kTile + kb * 16 + 4 * g + i;
-                    const bool ok = key < Nk && (!causal || key <= qi + off);
-                    s[kb][i] = ok ? s[kb][i] : -INFINITY;
-                }
-        }
-        float mx = s[0][0];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kb][i]);
-        mx = xor_max(mx);
-        const float mnew = fmaxf(mrun, mx);
-        const float ms = (mnew == -INFINITY) ? 0.f : mnew;
-        if (__builtin_amdgcn_ballot_w64(mnew != mrun) != 0) {
-            const float corr = fexp2((mrun - ms) * c);
-            lrun *= corr;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
-        }
-        bf16x8 pf[2];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float z = fexp2(exp_arg<false>(s[kb][i], ms, c));
-                lrun += z;
-                pf[kb >> 1][(kb & 1) * 4 + i] = to_bf16(z);
-            }
-        mrun = mnew;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[mb] = mfma_16x16x32(ld_tr_operand<D>(Vc, 32 * j, mb * 16, c16, g), pf[j],
-                                        acc[mb]);
-    };
-    auto step = [&](int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn, uint16_t* Vn) {
-        if (kt + 1 < kt1) {
-            dma.load(K + kvoff, Kn, (kt + 1) * kTile, Nk);
-            dma.load(V + kvoff, Vn, (kt + 1) * kTile, Nk);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (active) {
-            if (kt < nplain) compute(std::false_type{}, kt, Kc, Vc);
-            else compute(std::true_type{}, kt, Kc, Vc);
-        }
-        wait_vm_lgkm0<0>();
-        __builtin_amdgcn_s_barrier();
-    };
-    for (int kt = kt0; kt < kt1; kt += 2) {
-        step(kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        if (kt + 1 < kt1) step(kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
-    }
-
-    const float ltot = xor_sum(lrun);
-    if (r < rows) {
-        const size_t p = (size_t)split * ((size_t)Hq * total) + qrow;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            *reinterpret_cast<f32x4*>(Oacc + p * D + mb * 16 + 4 * g) = acc[mb];
-        if (g == 0) {
-            ML[2 * p] = mrun;
-            ML[2 * p + 1] = ltot;
-        }
-    }
-}
-
-// Merges the S <= kFewMaxSplits states of every row by the forward's rescale
-// rule and finishes as it does.  D/4 lanes share a row, 4 columns each: they read
-// the row maxima and sums of different splits at once and leave the weights in
-// LDS, then read the accumulators eight splits at a time, so the pass waits for
-// two round trips to memory and not for 2 S (20 us for 32 splits one after the
-// other, 6 us so).  A split that saw none of the row's keys has l = 0 (on the bits,
-// as in the kernels above); its weight is marked -1 and its accumulator, which
-// may hold anything, is not used.
+// Takes the states of every row together, in split order, and finishes as the
+// kernels above do.  D/4 lanes share a row, 4 columns each: they read the row
+// maxima and sums of all splits at once into LDS, then all accumulators, so the pass
+// waits for two round trips to memory and not for two per split (about 4 us,
+// whatever S).  items [sequence][key/value head][chunk of rows].
 template <int D>
 __global__ __launch_bounds__(256) void fwd_few_merge_kernel(
     const float* __restrict__ Oacc, const float* __restrict__ ML, uint16_t* __restrict__ O,
-    float* __restrict__ LSE, int Nmax, float scale, const int* __restrict__ cu, int Hq, int total,
-    int chunks, int S) {
-    constexpr int LPR = D / 4;         // lanes of a row
-    constexpr int RPB = 256 / LPR;     // rows of a workgroup
-    constexpr int MPL = kFewMaxSplits / LPR;
-    __shared__ float W[RPB][kFewMaxSplits];
-    const int prob = blockIdx.x / chunks;
+    float* __restrict__ LSE, int Nmax, float scale, int G, const int* __restrict__ cu, int Hq,
+    int total, const int* __restrict__ cu_k, int total_k, int Nkmax, int64_t state_rows,
+    int probs, int chunks) {
+    constexpr int LPR = D / 4;      // lanes of a row
+    constexpr int RPB = 256 / LPR;  // rows of a workgroup
+    __shared__ float M[RPB][kFewMaxSplits];
+    __shared__ float L[RPB][kFewMaxSplits];
     const int rl = threadIdx.x / LPR, j = threadIdx.x - rl * LPR;
-    const int qi = (blockIdx.x - prob * chunks) * RPB + rl, col = 4 * j;
-    const int seq = prob / Hq, h = prob - seq * Hq;
-    const int a = min(max(cu[seq], 0), total);
-    const int b = min(max(cu[seq + 1], a), total);
-    const bool have = qi < min(b - a, Nmax);
-    const size_t rows = (size_t)Hq * total;
-    const size_t row = (size_t)h * total + a + (have ? qi : 0);
+    const int col = 4 * j;
+    const int Hkv = Hq / G;
     const float c = scale * kLog2e;
-    float ms[MPL], ls[MPL], m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < MPL; ++i) {
-        const int sp = j + i * LPR;
-        ms[i] = -INFINITY;
-        ls[i] = 0.f;
-        if (have && sp < S) {
-            ms[i] = ML[2 * (sp * rows + row)];
-            ls[i] = ML[2 * (sp * rows + row) + 1];
+    for (uint32_t item = blockIdx.x; item < (uint32_t)probs * (uint32_t)chunks; item += gridDim.x) {
+        const int prob = (int)(item / (uint32_t)chunks);
+        const int seq = prob / Hkv, kvh = prob - seq * Hkv;
+        const SeqRows sr = seq_rows(cu, cu_k, seq * Hq + kvh * G, Nmax, Nkmax, G, Hq, total, total_k);
+        const int N = sr.nq, Nk = sr.nk;
+        const int rows = G * N;
+        const int r0 = (int)(item - (uint32_t)prob * (uint32_t)chunks) * RPB, r = r0 + rl;
+        if (!few_sequence(N, Nk, G) || r0 >= rows) continue;
+        const int tiles = (Nk + kTile - 1) / kTile;
+        const int chunk = few_chunk((rows + kTile - 1) / kTile, tiles);
+        const int S = (tiles + chunk - 1) / chunk;
+        const bool have = r < rows;
+        const size_t p = (size_t)kvh * state_rows +
+                         few_base(seq, sr.q0 - (size_t)kvh * G * total,
+                                  sr.kv0 - (size_t)kvh * total_k, G) + r;
+        static_assert(kFewMaxSplits <= LPR, "a lane per split");
+        if (have && j < S) {
+            M[rl][j] = ML[2 * (p + (size_t)j * rows)];
+            L[rl][j] = ML[2 * (p + (size_t)j * rows) + 1];
         }
-        m = fmaxf(m, ms[i]);
-    }
+        __syncthreads();
+        if (have) {
+            float m = -INFINITY, l = 0.f;
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+            f32x4 x[kFewMaxSplits];
 #pragma unroll
-    for (int x = 1; x < LPR; x *= 2) m = fmaxf(m, __shfl_xor(m, x));
-    const float msub = (m == -INFINITY) ? 0.f : m;
-    float l = 0.f;
+            for (int i = 0; i < kFewMaxSplits; ++i)
+                if (i < S)
+                    x[i] = *reinterpret_cast<const f32x4*>(Oacc + (p + (size_t)i * rows) * D + col);
 #pragma unroll
-    for (int i = 0; i < MPL; ++i) {
-        const bool seen = __float_as_uint(ls[i]) != 0u;
-        const float f = fexp2((ms[i] - msub) * c);
-        W[rl][j + i * LPR] = seen ? f : -1.f;
-        l += seen ? ls[i] * f : 0.f;
-    }
+            for (int i = 0; i < kFewMaxSplits; ++i) {
+                if (i >= S) break;
+                const float li = L[rl][i];
+                if (__float_as_uint(li) == 0u) continue;  // none of the row's keys
+                float w, wi;
+                few_weights(m, M[rl][i], c, w, wi);
+                l = __builtin_fmaf(li, wi, l * w);
 #pragma unroll
-    for (int x = 1; x < LPR; x *= 2) l += __shfl_xor(l, x);
-    __syncthreads();
-    if (!have) return;
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < S; s0 += 8) {
-        f32x4 x[8];
+                for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(x[i][e], wi, o[e] * w);
+            }
+            const size_t qrow = sr.q0 + (size_t)(r / N) * total + r % N;
+            const bool empty = __float_as_uint(l) == 0u;
+            float v[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (s0 + i < S)
-                x[i] = *reinterpret_cast<const f32x4*>(Oacc + ((s0 + i) * rows + row) * D + col);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (s0 + i >= S) break;
-            const float w = W[rl][s0 + i];
-            if (__float_as_uint(w) != 0xBF800000u) o += x[i] * w;
-        }
-    }
-    const bool empty = __float_as_uint(l) == 0u;
-    float v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = empty ? 0.f : o[i] / l;
-    st_bf16x4(O + row * D + col, v[0], v[1], v[2], v[3]);
-    if (j == 0) {
+            for (int i = 0; i < 4; ++i) v[i] = empty ? 0.f : o[i] / l;
+            st_bf16x4(O + qrow * D + col, v[0], v[1], v[2], v[3]);
+            if (j == 0) {
 #pragma clang fp contract(off)
-        const float lse = scale * m + logf(l);
-        LSE[row] = empty ? INFINITY : lse;
+                const float lse = scale * m + logf(l);
+                LSE[qrow] = empty ? INFINITY : lse;
+            }
+        }
+        __syncthreads();  // M and L have been read
     }
 }
 
 }  // namespace
 
-hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, float* Oacc,
-                          float* ML, int splits, const Shape& s, hipStream_t st) {
-    const int RT = (s.G * s.N + kTile - 1) / kTile;
-    dim3 grid((unsigned)(s.BH / s.G * RT * splits)), block(kThreads);
-#define GPA_FEW(DD)                                                                            \
-    launch_kernel(fwd_few_kernel<DD>, grid, block, st, Q, K, V, Oacc, ML, s.N, s.causal,       \
-                  s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk, splits)
-    if (s.d == 64) GPA_FEW(64); else GPA_FEW(128);
-#undef GPA_FEW
+namespace {
+
+// Workgroups that take few-query items in turn: enough to fill the chip several
+// times over, and few enough that a pack without such sequences does not wait for
+// their exits.
+constexpr int64_t kFewBlocks = 2048;
+
+// Most rows that a (sequence, key/value head) with few queries has.
+int few_most_rows(const Shape& s) {
+    const int64_t rows = (int64_t)s.G * (s.N < kFewQueries ? s.N : kFewQueries);
+    return (int)std::min<int64_t>(rows, std::max(kTile, s.Nk / kFewKeysPerRow));
+}
+
+// Places of a (sequence, key/value head): the most (row tile, split) pairs that any
+// sequence within the longest runs has.
+int few_places(const Shape& s, bool walk) {
+    const int most = (few_most_rows(s) + kTile - 1) / kTile;
+    const int tiles = (s.Nk + kTile - 1) / kTile;
+    if (walk) return most;
+    int places = 0;
+    for (int RT = 1; RT <= most; ++RT)
+        places = std::max(places, RT * std::min(kFewMaxSplits, (tiles + 4 * RT - 1) / (4 * RT)));
+    return places;
+}
+
+template <int D, Few FEW>
+hipError_t launch_fwd_as(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
+                         float* LSE, const Shape& s, hipStream_t st, FewArgs few) {
+    const int T = (s.N + kTile - 1) / kTile;
+    dim3 grid((unsigned)(s.BH * T)), block(kThreads);
+    const bool uneven = uneven_pack(s, s.total, s.N);
+    if (uneven) grid.x = packed_grid(s, s.total, s.N);
+    if constexpr (FEW != Few::kNone) {
+        few.places = few_places(s, FEW == Few::kWalk);
+        few.items = (uint32_t)(s.BH / s.G) * (uint32_t)few.places;
+        // a launch holds fewer than 2^32 threads, 2^24 workgroups of these
+        const int64_t room = (int64_t)0xFFFFFF - grid.x;
+        few.blocks = (int)std::max<int64_t>(1, std::min({(int64_t)few.items, kFewBlocks, room}));
+        grid.x += (unsigned)few.blocks;
+    }
+    const int Nk = s.Nk > 0 ? s.Nk : s.N;
+#define GPA_FWD(KERNEL, UN)                                                                    \
+    launch_kernel(KERNEL<D, false, UN, FEW>, grid, block, st, Q, K, V, O, LSE, s.BH, s.N,      \
+                  s.causal, s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, Nk, few)
+    // d = 64: one 16-query block per wave (measured faster); d = 128: two
+    // blocks per wave, whose halved LDS reads matter more there.
+    if constexpr (D == 64) {
+        if (uneven) GPA_FWD(fwd_sbs_q16_kernel, true);
+        else GPA_FWD(fwd_sbs_q16_kernel, false);
+    } else {
+        if (uneven) GPA_FWD(fwd_sbs_kernel, true);
+        else GPA_FWD(fwd_sbs_kernel, false);
+    }
+#undef GPA_FWD
     return hipGetLastError();
 }
 
-hipError_t launch_fwd_few_merge(const float* Oacc, const float* ML, uint16_t* O, float* LSE,
-                                int splits, const Shape& s, hipStream_t st) {
-    const int chunks = (s.N * (s.d / 4) + 255) / 256;  // workgroups of 1024 / d rows
-    dim3 grid((unsigned)(s.BH * chunks)), block(256);
-    if (s.d == 64)
-        launch_kernel(fwd_few_merge_kernel<64>, grid, block, st, Oacc, ML, O, LSE, s.N, s.scale,
-                      s.cu, s.Hq, s.total, chunks, splits);
-    else
-        launch_kernel(fwd_few_merge_kernel<128>, grid, block, st, Oacc, ML, O, LSE, s.N, s.scale,
-                      s.cu, s.Hq, s.total, chunks, splits);
-    return hipGetLastError();
-}
+}  // namespace
 
 hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
                       float* LSE, const Shape& s, hipStream_t st, bool fma_forward) {
-    const int T = (s.N + kTile - 1) / kTile;
+    if (!fma_forward)
+        return s.d == 64 ? launch_fwd_as<64, Few::kNone>(Q, K, V, O, LSE, s, st, {})
+                         : launch_fwd_as<128, Few::kNone>(Q, K, V, O, LSE, s, st, {});
+    const int T = (s.N + kTile - 1) / kTile;  // dense batches only
     dim3 grid((unsigned)(s.BH * T)), block(kThreads);
-    // d = 64: one 16-query block per wave (measured faster); d = 128: two
-    // blocks per wave, whose halved LDS reads matter more there.
-    const bool uneven = uneven_pack(s, s.total, s.N);
-    if (uneven) grid.x = packed_grid(s, s.total, s.N);
-#define GPA_FWD(KERNEL, DD, FM, UN)                                                           \
-    launch_kernel(KERNEL<DD, FM, UN>, grid, block, st, Q, K, V, O, LSE, s.BH, s.N, s.causal,      \
-                  s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk > 0 ? s.Nk : s.N)
-    if (s.d == 64) {
-        if (fma_forward) GPA_FWD(fwd_sbs_q16_kernel, 64, true, false);
-        else if (uneven) GPA_FWD(fwd_sbs_q16_kernel, 64, false, true);
-        else GPA_FWD(fwd_sbs_q16_kernel, 64, false, false);
-    } else {
-        if (fma_forward) GPA_FWD(fwd_sbs_kernel, 128, true, false);
-        else if (uneven) GPA_FWD(fwd_sbs_kernel, 128, false, true);
-        else GPA_FWD(fwd_sbs_kernel, 128, false, false);
-    }
-#undef GPA_FWD
+#define GPA_FMA(KERNEL, DD)                                                                    \
+    launch_kernel(KERNEL<DD, true, false, Few::kNone>, grid, block, st, Q, K, V, O, LSE, s.BH, \
+                  s.N, s.causal, s.scale, s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k,         \
+                  s.Nk > 0 ? s.Nk : s.N, FewArgs{})
+    if (s.d == 64) GPA_FMA(fwd_sbs_q16_kernel, 64); else GPA_FMA(fwd_sbs_kernel, 128);
+#undef GPA_FMA
+    return hipGetLastError();
+}
+
+hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
+                          float* LSE, float* Oacc, float* ML, const Shape& s, hipStream_t st) {
+    FewArgs few;
+    if (Oacc == nullptr)
+        return s.d == 64 ? launch_fwd_as<64, Few::kWalk>(Q, K, V, O, LSE, s, st, few)
+                         : launch_fwd_as<128, Few::kWalk>(Q, K, V, O, LSE, s, st, few);
+    few.Oacc = Oacc;
+    few.ML = ML;
+    few.rows = few_base(s.BH / s.Hq, s.total, s.total_k, s.G);
+    return s.d == 64 ? launch_fwd_as<64, Few::kSplit>(Q, K, V, O, LSE, s, st, few)
+                     : launch_fwd_as<128, Few::kSplit>(Q, K, V, O, LSE, s, st, few);
+}
+
+hipError_t launch_fwd_few_merge(const float* Oacc, const float* ML, uint16_t* O, float* LSE,
+                                const Shape& s, hipStream_t st) {
+    // chunks of 1024 / d rows: no more than key tiles, so probs * chunks < 2^31
+    const int chunks = (few_most_rows(s) * (s.d / 4) + 255) / 256;
+    const int probs = s.BH / s.G;
+    const int64_t items = (int64_t)probs * chunks;
+    dim3 grid((unsigned)std::min(items, kFewBlocks)), block(256);
+    const int64_t rows = few_base(s.BH / s.Hq, s.total, s.total_k, s.G);
+#define GPA_MERGE(DD)                                                                          \
+    launch_kernel(fwd_few_merge_kernel<DD>, grid, block, st, Oacc, ML, O, LSE, s.N, s.scale,   \
+                  s.G, s.cu, s.Hq, s.total, s.cu_k, s.total_k, s.Nk, rows, probs, chunks)
+    if (s.d == 64) GPA_MERGE(64); else GPA_MERGE(128);
+#undef GPA_MERGE
     return hipGetLastError();
 }
 

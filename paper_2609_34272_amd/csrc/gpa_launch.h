@@ -73,28 +73,49 @@ inline bool uneven_pack(const Shape& s, int total, int longest) {
     return s.cu != nullptr && (int64_t)(s.BH / s.Hq) * longest != total;
 }
 
-// Splits of the key tiles in the forward for few queries on long key runs of
-// packed sequences (fwd_few_kernel), or 0 where the ordinary forward runs.  It
-// takes at most 128 queries on at least 2048 keys, eight times as many keys as
-// queries (longest runs), where either the workgroups are too few to fill the
-// chip (then as many splits as bring them to kFewTarget, four key tiles or more
-// each) or a group of heads has rows for one 64-row tile at most and would read
-// its K and V once per head.  Measured, ordinary and split, us: 8 sequences of 4
-// queries on up to 5115 keys, 16 heads on 4, d = 128: 69 and 17; 4 of 128 on up
-// to 8192, 8 heads: 112 and 33; 24 of 1 on 8192, 32 heads on 8: 298 and 150; 16
-// of 64 on up to 2048, 16 heads on 4, d = 64: 22.6 and 20.1; with 24 of 16 on up
-// to 1024, 32 heads on 8, 14.2 and 18.3: the line at 2048 keys.  kFewTarget 512
-// is up to 18 % slower than 1024 where a sequence has few splits.
-constexpr int kFewMaxSplits = 32;
-inline int few_splits(const Shape& s) {
-    constexpr int64_t kFewTarget = 1024;
-    if (s.cu == nullptr || s.N > 128 || s.Nk < 2048 || s.Nk < 8 * s.N) return 0;
-    const int64_t base = (int64_t)(s.BH / s.G) * ((s.G * s.N + 63) / 64);
-    const int64_t most = (s.Nk + 255) / 256;
-    int64_t n = (kFewTarget + base - 1) / base;
-    if (n > most) n = most;
-    if (n > kFewMaxSplits) n = kFewMaxSplits;
-    return n >= 2 || (s.G > 1 && s.G * s.N <= 64) ? (int)n : 0;
+// Few queries on long key runs (new tokens against their past) in the forward of
+// packed sequences.  Which sequences are taken so, and how their keys are split,
+// follows from a sequence's own sizes alone: its bits depend neither on the
+// sequences beside it nor on the memory at hand.  The rows of a (sequence,
+// key/value head) are all G heads' queries, in row tiles of 64; a split has four
+// key tiles per row tile or more, and there are kFewMaxSplits at most.
+//
+// The lines, each with both sides measured (us, the ordinary forward and this one;
+// heads are query heads on key/value heads):
+// * 512 keys: 8 sequences of 4 queries on 520 to 660 keys, 16 heads on 4, d = 128,
+//   15.0 and 16.2; on 200 to 1999 keys 31.6 and 16.1 (21.5 with the line at 768).
+// * more than one row tile only with 16 keys per row or more, where the states cost
+//   little beside the products: 24 of 128 on 3592 to 8192, 32 heads on 8, d = 64, 253
+//   and 302 where every length is split, 268 with this line (most of those are
+//   ordinary).  One row tile gains at any length above 512: 24 of 16 on 800 to 1030,
+//   32 heads on 8, d = 128, 44 and 35.
+// * 8 splits: 16 are no faster where the chip has room (19.9 us and 22.8 for 8 of 4 on
+//   406 to 5115 keys) and slower where it has none (337 and 370 for 128 of 1 on up to
+//   4096, 32 heads on 8, d = 128).
+constexpr int kFewQueries = 128;
+constexpr int kFewKeys = 512;
+constexpr int kFewMaxSplits = 8;
+constexpr int kFewKeysPerRow = 16;
+__host__ __device__ constexpr bool few_sequence(int nq, int nk, int G) {
+    return nq <= kFewQueries && nk >= kFewKeys &&
+           ((int64_t)G * nq <= 64 || (int64_t)G * nq <= nk / kFewKeysPerRow);
+}
+// Key tiles of a split of a sequence with `tiles` key tiles and RT row tiles.
+__host__ __device__ constexpr int few_chunk(int RT, int tiles) {
+    const int most = (tiles + kFewMaxSplits - 1) / kFewMaxSplits;
+    return 4 * RT > most ? 4 * RT : most;
+}
+// First state row of sequence `seq`, whose queries and keys begin at `a` and `ak`,
+// among the state rows of a key/value head; at seq = nseq, a = total_q, ak =
+// total_k the number of them.  A sequence of R rows, nk keys in t tiles and S
+// splits has R S <= R (t / 4 RT + 1) <= 16 t + R < nk / 4 + 16 + R state rows, and
+// the next one begins nk / 4 - 3/4 + R + 17 or more further on.
+__host__ __device__ inline int64_t few_base(int64_t seq, int64_t a, int64_t ak, int64_t G) {
+    return ak / 4 + G * (a < kFewQueries * seq ? a : kFewQueries * seq) + 17 * seq;
+}
+// Whether a call may hold such sequences (one set of offsets has nq == nk).
+inline bool may_have_few(const Shape& s) {
+    return s.cu != nullptr && s.cu_k != s.cu && s.Nk >= kFewKeys;
 }
 
 // Workgroups of the UNEVEN instantiations for one side: one place per tile (a
@@ -130,13 +151,16 @@ enum KernelId {
 hipError_t launch_fwd(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
                       float* LSE, const Shape& s, hipStream_t st, bool fma_forward = false);
 
-// Forward for few queries on long key runs: per split the FP32 accumulators
-// Oacc [splits, Hq, total, d] and the row maximum and sum ML [splits, Hq, total,
-// 2]; the second launcher merges them into O and LSE.
-hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, float* Oacc,
-                          float* ML, int splits, const Shape& s, hipStream_t st);
+// Forward of packed sequences that takes those with few queries on long key runs
+// by splits of their keys (few_sequence).  With a workspace every split leaves its
+// FP32 accumulators in Oacc [Hkv, rows, d] and its row maxima and sums in ML [Hkv,
+// rows, 2] (rows = few_base of the ends), and the second launcher merges them into
+// O and LSE; with both null one workgroup takes a row tile's splits in turn, with
+// the same results.
+hipError_t launch_fwd_few(const uint16_t* Q, const uint16_t* K, const uint16_t* V, uint16_t* O,
+                          float* LSE, float* Oacc, float* ML, const Shape& s, hipStream_t st);
 hipError_t launch_fwd_few_merge(const float* Oacc, const float* ML, uint16_t* O, float* LSE,
-                                int splits, const Shape& s, hipStream_t st);
+                                const Shape& s, hipStream_t st);
 
 // Query-major pass: writes D = rowsum(dO * O) and dQ; in the gproj modes also
 // rho, m, lambda (zero in plain mode); in gproj mode also Z = BF16(-lambda Q)

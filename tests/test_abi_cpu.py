@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -189,27 +190,29 @@ def test_varlen_validation(lib):
                                    1, 0.125, 2, P + 0xA0000000, 16, None) == 3
 
 
+def _few(nq, nk, G):
+    """The sequences whose keys the forward with a workspace splits, and their
+    (rows, row tiles, splits)."""
+    R = G * nq
+    if not (0 < nq <= 128 and nk >= 512 and (R <= 64 or R <= nk // 16)):
+        return None
+    RT, tiles = -(-R // 64), -(-nk // 64)
+    chunk = max(4 * RT, -(-tiles // 8))
+    return R, RT, -(-tiles // chunk)
+
+
 def test_few_query_forward_workspace_and_validation(lib):
-    """Which packed shapes take the split forward, the bytes it asks for, and its
-    host-side checks."""
+    """The workspace that the forward with split keys asks for, and its host-side
+    checks."""
     f = lib.gpa_attn_fwd_varlen_workspace_bytes
     few = (8, 32, 30000, 16, 4, 4, 5115, 128)  # 8 sequences of 4 queries
     n = f(*few)
-    splits = 5115 // 256 + 1                   # four key tiles or more each
-    assert n == splits * 16 * 32 * (128 + 2) * 4
-    # the ordinary forward: short keys, many queries, too few keys per query,
-    # enough workgroups without a group to share
-    assert f(8, 32, 8000, 16, 4, 4, 2047, 128) == 0
-    assert f(8, 1032, 30000, 16, 4, 129, 5115, 128) == 0
-    assert f(4, 512, 8000, 16, 4, 128, 2048 - 1, 128) == 0
-    assert f(2, 600, 6000, 16, 4, 300, 2400, 64) == 0
-    assert f(64, 64, 128000, 32, 32, 1, 2048, 64) == 0
-    # a group's rows in one tile: one pass over K and V even without splits
-    assert f(128, 1024, 256000, 32, 8, 8, 2048, 128) == 1024 * 32 * (128 + 2) * 4
-    # no more than kFewTarget workgroups' worth of rows beyond the rows themselves
-    for nseq, q in ((1, 1), (3, 128), (400, 100)):
-        rows = nseq * q * 16
-        assert f(nseq, nseq * q, nseq * 4096, 16, 16, q, 4096, 64) <= (64 * 1024 + 2 * rows) * 66 * 4 + 512
+    rows = 4 * (30000 // 4 + 4 * 32 + 17 * 8)
+    assert n == rows * 128 * 4 + -(-rows * 8 // 256) * 256
+    # no key run is long enough to be split
+    assert f(8, 32, 4000, 16, 4, 4, 511, 128) == 0 and f(8, 32, 4000, 16, 4, 4, 512, 128) > 0
+    # whether there are few queries is a matter of each sequence, not of the longest
+    assert f(8, 1032, 30000, 16, 4, 129, 5115, 128) > 0
     # invalid shapes
     assert f(0, 32, 30000, 16, 4, 4, 5115, 128) == 0
     assert f(8, 32, 30000, 16, 5, 4, 5115, 128) == 0
@@ -227,3 +230,32 @@ def test_few_query_forward_workspace_and_validation(lib):
     assert call(O=FAKE + 0x90000000) == 1                 # O overlaps the workspace
     assert call(ws=FAKE + 0x50000000) == 1                # overlaps the offsets
     assert call(cu=None) == 1 and call(O=None) == 1
+    # no workspace at all is allowed (the splits one after the other): the next
+    # check, of the buffers, is reached
+    assert call(ws=None, ws_bytes=0, O=None) == 1
+    assert call(ws=FAKE + 0x90000000, ws_bytes=0) == 3
+
+
+def test_few_query_states_fit_their_workspace(lib):
+    """The state rows of a pack's split sequences lie one behind the other inside
+    the workspace, whatever the lengths: sequence s begins at row
+    ak/4 + G min(a, 128 s) + 17 s of its key/value head (a, ak: its first query and
+    key)."""
+    rng = np.random.default_rng(0)
+    for _ in range(300):
+        nseq, Hkv, G = int(rng.integers(1, 40)), int(rng.integers(1, 5)), int(rng.integers(1, 9))
+        top = int(np.exp(rng.uniform(np.log(1), np.log(400))))
+        nq = rng.integers(0, top + 1, nseq)
+        nk = np.exp(rng.uniform(0, np.log(20000), nseq)).astype(int) - 1
+        nq[0], nk[0] = max(1, nq[0]), max(512, nk[0])
+        nbytes = lib.gpa_attn_fwd_varlen_workspace_bytes(
+            nseq, int(nq.sum()), int(nk.sum()), Hkv * G, Hkv, int(nq.max()), int(nk.max()), 64)
+        a, ak, end = 0, 0, 0
+        for s in range(nseq):
+            base = ak // 4 + G * min(a, 128 * s) + 17 * s
+            assert base >= end
+            shape = _few(int(nq[s]), int(nk[s]), G)
+            if shape:
+                end = base + shape[0] * shape[2]
+            a, ak = a + int(nq[s]), ak + int(nk[s])
+        assert Hkv * end * (64 + 2) * 4 <= nbytes
