@@ -106,3 +106,105 @@ def test_without_memory_for_the_workspace_the_bits_are_the_same(gpa, monkeypatch
     assert refused
     for s in want:
         assert all(torch.equal(a, b) for a, b in zip(want[s], got[s]))
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 4, 64), (16, 4, 128), (16, 4, 64), (8, 1, 128)])
+def test_calls_stay_inside_their_buffers(gpa, Hq, Hkv, d):
+    """O, LSE and a workspace of exactly the reported size between guard regions,
+    with the workspace full of NaN bytes: guards intact, every row of O and LSE
+    written, the bits of a call with a zeroed workspace."""
+    sel = list(range(len(RUNS)))
+    p = Pack(RUNS, Hq, Hkv, d, 77)
+    q, k, v, cu, mq, ck, mk = p.args(sel)
+    L, guard = gpa.lib(), 4096
+    shape = (len(sel), q.shape[1], k.shape[1], Hq, Hkv, mq, mk, d)
+    n = {"O": 2 * q.numel(), "LSE": 4 * Hq * q.shape[1],
+         "workspace": L.gpa_attn_fwd_varlen_workspace_bytes(*shape)}
+    assert n["workspace"] > 0
+    for causal in (True, False):
+        want = p.run_c(gpa, sel, causal, torch.zeros(n["workspace"], dtype=torch.uint8, device="cuda"))
+        buf = {name: torch.full((b + 2 * guard,), 0xA5, dtype=torch.uint8, device="cuda")
+               for name, b in n.items()}
+        for name, b in n.items():
+            buf[name][guard:guard + b] = 0xFF
+        at = {name: b.data_ptr() + guard for name, b in buf.items()}
+        rc = L.gpa_attn_fwd_varlen_ws(
+            q.data_ptr(), k.data_ptr(), v.data_ptr(), at["O"], at["LSE"], cu.data_ptr(),
+            ck.data_ptr(), *shape, int(causal), 1 / math.sqrt(d), at["workspace"], n["workspace"],
+            torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        for name, b in buf.items():
+            assert (b[:guard] == 0xA5).all() and (b[guard + n[name]:] == 0xA5).all(), name
+        o = buf["O"][guard:guard + n["O"]].view(torch.bfloat16).view(q.shape)
+        lse = buf["LSE"][guard:guard + n["LSE"]].view(torch.float32).view(q.shape[:2])
+        for s, (a, b) in p.split(o, lse, sel).items():
+            assert not torch.isnan(a.float()).any() and not torch.isnan(b).any(), s
+            assert torch.equal(a, want[s][0]) and torch.equal(b, want[s][1]), s
+
+
+@pytest.mark.parametrize("value", [math.nan, math.inf, -math.inf])
+@pytest.mark.parametrize("which", ["Q", "K", "V"])
+def test_non_finite_inputs_reach_what_depends_on_them(gpa, which, value):
+    """In one query, or in one early key of one key/value head, of a split sequence:
+    the outputs that depend on it are not finite, and those of the other queries or
+    heads and of the other sequences keep their bits."""
+    p = Pack([(4, 3000), (20, 5000), (2, 100)], 8, 2, 64, 5)
+    sel = [0, 1, 2]
+    want = p.run(gpa, sel, True)
+    x = p.parts[1]["QKV".index(which)]
+    if which == "Q":
+        x[3, 7, 5] = value
+    else:
+        x[1, 100, 5] = value
+    got = p.run(gpa, sel, True)
+    for s in (0, 2):
+        assert all(torch.equal(a, b) for a, b in zip(want[s], got[s]))
+    (o, lse), (o1, lse1) = want[1], got[1]
+    hit = torch.zeros(8, 20, dtype=torch.bool, device="cuda")
+    if which == "Q":
+        hit[3, 7] = True
+    else:
+        hit[4:] = True  # the heads of the group see key 100
+    assert torch.equal(o[~hit], o1[~hit]) and torch.equal(lse[~hit], lse1[~hit])
+    assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
+    bad = ~torch.isfinite(o1.float())
+    if which == "V":  # the column alone, and not the LSE
+        assert bad[hit][:, 5].all() and torch.equal(lse, lse1)
+        bad[..., 5] = False
+        assert not bad.any()
+    elif which == "Q" or math.isnan(value):
+        assert bad[hit].all()
+        assert not torch.isfinite(lse1[hit]).any()
+    else:  # an infinite key: logits of either sign, +inf gives no finite result
+        logit = p.parts[1][0][4:, :, 5].float() * value
+        assert bad[4:][logit > 0].all()
+        assert torch.isfinite(o1[4:][logit < 0].float()).all()
+
+
+def test_captured_in_a_graph(gpa):
+    p = Pack([(4, 3000), (1, 300), (40, 2000), (300, 300)], 8, 2, 128, 9)
+    q, k, v, cu, mq, ck, mk = p.args([0, 1, 2, 3])
+
+    def step():
+        return gpa.attn_fwd_varlen(q, k, v, cu, mq, True, cu_seqlens_k=ck, max_seqlen_k=mk)
+
+    ref = [t.clone() for t in step()]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = step()
+    noise = torch.randn(1 << 18, device="cuda")
+    for _ in range(3):
+        noise.mul_(0.9999).sum()
+        for t in out:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, ref))

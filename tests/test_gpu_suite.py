@@ -320,10 +320,11 @@ def test_varlen_rejects_bad_arguments(gpa):
                             max_seqlen_k=case.total + 1)
 
 
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv,causal,reps", [
     (8, 8, True, 5), (16, 2, True, 5), (16, 16, False, 5), (3, 1, True, 5), (12, 4, False, 5),
     (8, 4, True, 9), (3, 3, False, 9), (16, 4, True, 0), (1, 1, True, 0)])
-def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal, reps):
+def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal, reps, d):
     """Packs of unequal runs deal their heads over the XCDs when Hq is a
     multiple of 8 and rotate them otherwise, in groups of sequences, and search
     among 64 sequences at most (reps = 9 has 74): every problem's rows still
@@ -332,7 +333,7 @@ def test_uneven_pack_equals_single_sequences(gpa, Hq, Hkv, causal, reps):
     lens = [1, 300, 64, 0, 129, 5, 190, 63] * reps + [700, 65]
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     g = torch.Generator().manual_seed(Hq)
-    total, d = int(cu[-1]), 64
+    total = int(cu[-1])
 
     def draw(h):
         return torch.randn(h, total, d, generator=g).to(torch.bfloat16).cuda()
