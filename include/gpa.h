@@ -342,9 +342,8 @@ gpa_status gpa_attn_bwd_varlen(const uint16_t* Q, const uint16_t* K, const uint1
  * operand of a matrix product rounded below FP32).  BF16 inputs are multiplied
  * as they are (their products are exact in FP32); the FP32 probabilities and
  * score gradients enter their products as three BF16 parts that add up to them
- * exactly; every accumulation is FP32.  Inputs that are not finite give results
- * that are not finite (an infinity may come back as a NaN).  One call runs
- * forward and backward:
+ * exactly; every accumulation is FP32.  Infinities and NaNs come out as FP32
+ * products give them.  One call runs forward and backward:
  * In : Q, K, V, dO [B,H,N,d] BF16.
  * Out: O, dQ, dK, dV [B,H,N,d] BF16 (RNE casts of FP32 results); LSE [B,H,N] FP32.
  * The FP32 output (not its BF16 cast) feeds the backward's D = rowsum(dO O).

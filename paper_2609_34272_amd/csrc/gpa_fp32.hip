@@ -76,17 +76,24 @@ __device__ __forceinline__ f32x4 block_dot(const uint16_t* X, int r0, const bf16
 // The three BF16 parts of 8 FP32 values, x = hi + mid + lo exactly (24 bits of
 // significand in three times 8): each part is the upper half of what the parts
 // before it leave, which an FP32 subtraction gives exactly.  Five vector
-// instructions per value and a half; a value that is not finite gives parts
-// that are not.
+// instructions per value and a half.  A value that is not finite gives a mid part
+// that is a NaN; EXACT_INF gives it as its hi part alone.
 struct Split {
     bf16x8 hi, mid, lo;
 };
+__device__ __forceinline__ bool is_finite(float x) {
+    return (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u;
+}
+__device__ __forceinline__ bool is_nan(float x) {
+    return (__float_as_uint(x) & 0x7FFFFFFFu) > 0x7F800000u;
+}
 __device__ __forceinline__ float upper(float x) {
     return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
 }
 __device__ __forceinline__ uint32_t uppers(float a, float b) {  // b's upper half above a's
     return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
 }
+template <bool EXACT_INF>
 __device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
     u32x4 h, m, l;
 #pragma unroll
@@ -96,6 +103,7 @@ __device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             r[e] = x[e] - upper(x[e]);
+            if (EXACT_INF && !is_finite(x[e])) r[e] = 0.f;
             q[e] = r[e] - upper(r[e]);
         }
         h[j] = uppers(x[0], x[1]);
@@ -109,25 +117,55 @@ __device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
 // values b[kb][i] belong to row 16 kb + 4 g + i and X is a row-major swizzled
 // BF16 tile: the transpose read gives lane (c16, g) X[32 kb2 + 4 g + r][16 mb +
 // c16] and X[32 kb2 + 16 + 4 g + r][...] for r = 0..3.
-template <int D>
+//
+// A factor whose mid or lo part is 0 turns an infinity of X into a NaN, and so does
+// an infinite factor.  A pass that ends with a NaN in its accumulators therefore
+// runs again with EXACT_INF (any_nan): values of X that are not finite then meet the
+// hi part alone, which has the factor's sign and is 0 where it is, so the products
+// are the infinities and NaNs of one FP32 product, and all others what they were.
+template <int D, bool EXACT_INF>
 __device__ __forceinline__ void tr_accumulate(const uint16_t* X, const f32x4 (&b)[4],
                                               f32x4 (&acc)[D / 16], int c16, int g) {
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
-        const Split p = split3(b[2 * kb2], b[2 * kb2 + 1]);
+        const Split p = split3<EXACT_INF>(b[2 * kb2], b[2 * kb2 + 1]);
 #pragma unroll
         for (int mb = 0; mb < D / 16; ++mb) {
             const bf16x8 t = ld_tr_operand<D>(X, 32 * kb2, 16 * mb, c16, g);
-            acc[mb] = mfma_16x16x32(t, p.lo, acc[mb]);
-            acc[mb] = mfma_16x16x32(t, p.mid, acc[mb]);
+            bf16x8 f = t;
+            if constexpr (EXACT_INF)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) f[i] = is_finite(bf16_to_f32(t[i])) ? t[i] : (__bf16)0.f;
+            acc[mb] = mfma_16x16x32(f, p.lo, acc[mb]);
+            acc[mb] = mfma_16x16x32(f, p.mid, acc[mb]);
             acc[mb] = mfma_16x16x32(t, p.hi, acc[mb]);
         }
     }
 }
 
+template <int MB>
+__device__ __forceinline__ bool any_nan(const f32x4 (&acc)[MB]) {
+    bool nan = false;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nan |= is_nan(acc[mb][i]);
+    return nan;
+}
+// Whether x holds in any lane of the workgroup.  `lds`: a word per wave, free.
+__device__ __forceinline__ bool workgroup_any(bool x, void* lds, int wave) {
+    volatile int* w = reinterpret_cast<volatile int*>(lds);
+    const bool any = __builtin_amdgcn_ballot_w64(x) != 0;
+    if ((threadIdx.x & 63) == 0) w[wave] = any;
+    __syncthreads();
+    const bool all = (w[0] | w[1] | w[2] | w[3]) != 0;
+    __syncthreads();
+    return all;
+}
+
 // ------------------------------------------------------------------ forward
 template <int D>
-__global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, float* __restrict__ O32, uint16_t* __restrict__ O,
     float* __restrict__ LSE, float* __restrict__ Mrow, float* __restrict__ Linv, int BH, int N,
@@ -151,80 +189,87 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
     const KeyRange kr = key_range(tile, N, 0, causal);
     const int nkv = kr.nkv, nplain = kr.nplain;
     const float lg = kLog2e;
-    float mrun = -INFINITY, lrun = 0.f;  // scaled running maximum; this lane's share of l
+    float mrun, lrun;  // scaled running maximum; this lane's share of l
     f32x4 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     TileDma<D> dma;
     dma.init(lane, wave);
-    dma.load(K + hoff, KV0[0], 0, N);
-    dma.load(V + hoff, KV0[1], 0, N);
-    wait_vm_lgkm0<0>();
-    __syncthreads();
 
-    auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
-                    uint16_t* Vn) {
-        constexpr bool MASK = decltype(masked)::value;
-        if (kt + 1 < nkv) {
-            dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
-            dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4 s[4];
-        float tmax = -INFINITY;
+    auto walk = [&](auto exact_inf) {
+        mrun = -INFINITY;
+        lrun = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            s[kb] = block_dot<D>(Kc, 16 * kb, qf, c16, g);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float v = scale * s[kb][i];
-                if constexpr (MASK) {
-                    const int key = kt * kTile + 16 * kb + 4 * g + i;
-                    v = (key < N && (!causal || key <= qrow)) ? v : -INFINITY;
-                }
-                s[kb][i] = v;
-                tmax = fmaxf(tmax, v);
-            }
-        }
-        const float mnew = fmaxf(mrun, xor_max(tmax));
-        // a row that has seen no key yet keeps m = -inf; its factors are 1, 0
-        const float corr = mnew == -INFINITY ? 1.f : fexp2((mrun - mnew) * lg);
-        const float msub = mnew == -INFINITY ? 0.f : mnew;
-        mrun = mnew;
-        float lsum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float p = fexp2((s[kb][i] - msub) * lg);
-                s[kb][i] = p;
-                lsum += p;
-            }
-        lrun = lrun * corr + lsum;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
-        tr_accumulate<D>(Vc, s, acc, c16, g);
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        dma.load(K + hoff, KV0[0], 0, N);
+        dma.load(V + hoff, KV0[1], 0, N);
         wait_vm_lgkm0<0>();
         __syncthreads();
+
+        auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
+                        uint16_t* Vn) {
+            constexpr bool MASK = decltype(masked)::value;
+            if (kt + 1 < nkv) {
+                dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
+                dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 s[4];
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                s[kb] = block_dot<D>(Kc, 16 * kb, qf, c16, g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float v = scale * s[kb][i];
+                    if constexpr (MASK) {
+                        const int key = kt * kTile + 16 * kb + 4 * g + i;
+                        v = (key < N && (!causal || key <= qrow)) ? v : -INFINITY;
+                    }
+                    s[kb][i] = v;
+                    tmax = fmaxf(tmax, v);
+                }
+            }
+            const float mnew = fmaxf(mrun, xor_max(tmax));
+            // a row that has seen no key yet keeps m = -inf; its factors are 1, 0
+            const float corr = mnew == -INFINITY ? 1.f : fexp2((mrun - mnew) * lg);
+            const float msub = mnew == -INFINITY ? 0.f : mnew;
+            mrun = mnew;
+            float lsum = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float p = fexp2((s[kb][i] - msub) * lg);
+                    s[kb][i] = p;
+                    lsum += p;
+                }
+            lrun = lrun * corr + lsum;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
+            tr_accumulate<D, decltype(exact_inf)::value>(Vc, s, acc, c16, g);
+            wait_vm_lgkm0<0>();
+            __syncthreads();
+        };
+        const std::false_type plain;
+        const std::true_type masked;
+        int kt = 0;
+        for (; kt + 1 < nplain; kt += 2) {
+            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+            step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+        }
+        if (kt < nplain) {
+            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+            ++kt;
+        }
+        // Tile kt lives in buffer kt mod 2.
+        // At most one tile needs masks: the diagonal one, or the key tail.
+        if (kt < nkv) {
+            if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
+            else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        }
     };
-    const std::false_type plain;
-    const std::true_type masked;
-    int kt = 0;
-    for (; kt + 1 < nplain; kt += 2) {
-        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
-    }
-    if (kt < nplain) {
-        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        ++kt;
-    }
-    // Tile kt lives in buffer kt mod 2.
-    // At most one tile needs masks: the diagonal one, or the key tail.
-    if (kt < nkv) {
-        if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-        else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-    }
+    walk(std::false_type{});
+    if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
 
     const float l = xor_sum(lrun);
     if (qrow < N) {
@@ -250,7 +295,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(
 
 // ------------------------------------------------------- query-major pass
 template <int D>
-__global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
     const float* __restrict__ O32, const float* __restrict__ Mrow,
@@ -297,62 +342,66 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
     const KeyRange kr = key_range(tile, N, 0, causal);
     const int nkv = kr.nkv, nplain = kr.nplain;
     f32x4 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     TileDma<D> dma;
     dma.init(lane, wave);
     wait_vm_lgkm0<0>();
-    dma.load(K + hoff, KV0[0], 0, N);
-    dma.load(V + hoff, KV0[1], 0, N);
-    wait_vm_lgkm0<0>();
-    __syncthreads();
-
-    auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
-                    uint16_t* Vn) {
-        constexpr bool MASK = decltype(masked)::value;
-        if (kt + 1 < nkv) {
-            dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
-            dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4 ds[4];
+    auto walk = [&](auto exact_inf) {
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            const f32x4 s = block_dot<D>(Kc, 16 * kb, qf, c16, g);
-            const f32x4 dp = block_dot<D>(Vc, 16 * kb, uf, c16, g);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float p = fexp2((scale * s[i] - mi) * lg) * li;
-                if constexpr (MASK) {
-                    const int key = kt * kTile + 16 * kb + 4 * g + i;
-                    p = (key < N && (!causal || key <= qrow)) ? p : 0.f;
-                }
-                ds[kb][i] = p * (dp[i] - Di);
-                if constexpr (MASK) ds[kb][i] = p != 0.f ? ds[kb][i] : 0.f;
-            }
-        }
-        tr_accumulate<D>(Kc, ds, acc, c16, g);
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        dma.load(K + hoff, KV0[0], 0, N);
+        dma.load(V + hoff, KV0[1], 0, N);
         wait_vm_lgkm0<0>();
         __syncthreads();
+
+        auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
+                        uint16_t* Vn) {
+            constexpr bool MASK = decltype(masked)::value;
+            if (kt + 1 < nkv) {
+                dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
+                dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 ds[4];
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                const f32x4 s = block_dot<D>(Kc, 16 * kb, qf, c16, g);
+                const f32x4 dp = block_dot<D>(Vc, 16 * kb, uf, c16, g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float p = fexp2((scale * s[i] - mi) * lg) * li;
+                    if constexpr (MASK) {
+                        const int key = kt * kTile + 16 * kb + 4 * g + i;
+                        p = (key < N && (!causal || key <= qrow)) ? p : 0.f;
+                    }
+                    ds[kb][i] = p * (dp[i] - Di);
+                    if constexpr (MASK) ds[kb][i] = p != 0.f ? ds[kb][i] : 0.f;
+                }
+            }
+            tr_accumulate<D, decltype(exact_inf)::value>(Kc, ds, acc, c16, g);
+            wait_vm_lgkm0<0>();
+            __syncthreads();
+        };
+        const std::false_type plain;
+        const std::true_type masked;
+        int kt = 0;
+        for (; kt + 1 < nplain; kt += 2) {
+            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+            step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+        }
+        if (kt < nplain) {
+            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+            ++kt;
+        }
+        // Tile kt lives in buffer kt mod 2.
+        // At most one tile needs masks: the diagonal one, or the key tail.
+        if (kt < nkv) {
+            if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
+            else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        }
     };
-    const std::false_type plain;
-    const std::true_type masked;
-    int kt = 0;
-    for (; kt + 1 < nplain; kt += 2) {
-        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
-    }
-    if (kt < nplain) {
-        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        ++kt;
-    }
-    // Tile kt lives in buffer kt mod 2.
-    // At most one tile needs masks: the diagonal one, or the key tail.
-    if (kt < nkv) {
-        if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-        else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-    }
+    walk(std::false_type{});
+    if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
 
     if (qok) {
         uint16_t* drow = dQ + hoff + (size_t)qrow * D;
@@ -372,7 +421,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(
 
 // --------------------------------------------------------- key-major pass
 template <int D>
-__global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
     const float* __restrict__ TS, uint16_t* __restrict__ dK, uint16_t* __restrict__ dV, int BH,
@@ -399,11 +448,6 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
     const float* tsh = TS + (size_t)bh * T * kF32Stat;
 
     f32x4 accV[MB], accK[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        accV[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        accK[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
     const int qt0 = causal ? tile : 0;  // the diagonal tile first, masked
 
     TileDma<D> dma;
@@ -420,59 +464,68 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkdv_kernel(
                      lds_addr(ST + wave * kTile), (uint32_t)lane * 4u);
     };
     wait_vm_lgkm0<0>();
-    fill(qt0 < T ? qt0 : 0, QU0, ST0);
-    wait_vm_lgkm0<0>();
-    __syncthreads();
-
-    auto step = [&](auto masked, int qt, uint16_t (*QUc)[kTile * D], const float* st,
-                    uint16_t (*QUn)[kTile * D], float* STn) {
-        constexpr bool MASK = decltype(masked)::value;
-        const uint16_t* Qc = QUc[0];
-        const uint16_t* Uc = QUc[1];
-        if (qt + 1 < T) fill(qt + 1, QUn, STn);
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4 p[4], ds[4];
+    auto walk = [&](auto exact_inf) {
 #pragma unroll
-        for (int qb = 0; qb < 4; ++qb) {
-            const f32x4 mq = *reinterpret_cast<const f32x4*>(st + 16 * qb + 4 * g);
-            const f32x4 lq = *reinterpret_cast<const f32x4*>(st + kTile + 16 * qb + 4 * g);
-            const f32x4 dq = *reinterpret_cast<const f32x4*>(st + 2 * kTile + 16 * qb + 4 * g);
-            const f32x4 s = block_dot<D>(Qc, 16 * qb, kf, c16, g);
-            const f32x4 dp = block_dot<D>(Uc, 16 * qb, vf, c16, g);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float pv = fexp2((scale * s[i] - mq[i]) * lg) * lq[i];
-                if constexpr (MASK) {
-                    const int query = qt * kTile + 16 * qb + 4 * g + i;
-                    pv = (!causal || krow <= query) ? pv : 0.f;
-                }
-                p[qb][i] = pv;
-                ds[qb][i] = pv * (dp[i] - dq[i]);
-                if constexpr (MASK) ds[qb][i] = pv != 0.f ? ds[qb][i] : 0.f;
-            }
+        for (int mb = 0; mb < MB; ++mb) {
+            accV[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            accK[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        tr_accumulate<D>(Uc, p, accV, c16, g);
-        tr_accumulate<D>(Qc, ds, accK, c16, g);
+        fill(qt0 < T ? qt0 : 0, QU0, ST0);
         wait_vm_lgkm0<0>();
         __syncthreads();
+
+        auto step = [&](auto masked, int qt, uint16_t (*QUc)[kTile * D], const float* st,
+                        uint16_t (*QUn)[kTile * D], float* STn) {
+            constexpr bool MASK = decltype(masked)::value;
+            const uint16_t* Qc = QUc[0];
+            const uint16_t* Uc = QUc[1];
+            if (qt + 1 < T) fill(qt + 1, QUn, STn);
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 p[4], ds[4];
+#pragma unroll
+            for (int qb = 0; qb < 4; ++qb) {
+                const f32x4 mq = *reinterpret_cast<const f32x4*>(st + 16 * qb + 4 * g);
+                const f32x4 lq = *reinterpret_cast<const f32x4*>(st + kTile + 16 * qb + 4 * g);
+                const f32x4 dq = *reinterpret_cast<const f32x4*>(st + 2 * kTile + 16 * qb + 4 * g);
+                const f32x4 s = block_dot<D>(Qc, 16 * qb, kf, c16, g);
+                const f32x4 dp = block_dot<D>(Uc, 16 * qb, vf, c16, g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float pv = fexp2((scale * s[i] - mq[i]) * lg) * lq[i];
+                    if constexpr (MASK) {
+                        const int query = qt * kTile + 16 * qb + 4 * g + i;
+                        pv = (!causal || krow <= query) ? pv : 0.f;
+                    }
+                    p[qb][i] = pv;
+                    ds[qb][i] = pv * (dp[i] - dq[i]);
+                    if constexpr (MASK) ds[qb][i] = pv != 0.f ? ds[qb][i] : 0.f;
+                }
+            }
+            tr_accumulate<D, decltype(exact_inf)::value>(Uc, p, accV, c16, g);
+            tr_accumulate<D, decltype(exact_inf)::value>(Qc, ds, accK, c16, g);
+            wait_vm_lgkm0<0>();
+            __syncthreads();
+        };
+        const std::false_type plain;
+        const std::true_type masked;
+        int qt = qt0;
+        // The first tile is staged in slot 0 whatever its index: slots alternate
+        // with the step count from qt0.
+        if (causal && qt < T) {
+            step(masked, qt, QU0, ST0, QU1, ST1);
+            ++qt;
+        } else if (qt < T) {
+            step(plain, qt, QU0, ST0, QU1, ST1);
+            ++qt;
+        }
+        for (; qt + 1 < T; qt += 2) {
+            step(plain, qt, QU1, ST1, QU0, ST0);
+            step(plain, qt + 1, QU0, ST0, QU1, ST1);
+        }
+        if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
     };
-    const std::false_type plain;
-    const std::true_type masked;
-    int qt = qt0;
-    // The first tile is staged in slot 0 whatever its index: slots alternate
-    // with the step count from qt0.
-    if (causal && qt < T) {
-        step(masked, qt, QU0, ST0, QU1, ST1);
-        ++qt;
-    } else if (qt < T) {
-        step(plain, qt, QU0, ST0, QU1, ST1);
-        ++qt;
-    }
-    for (; qt + 1 < T; qt += 2) {
-        step(plain, qt, QU1, ST1, QU0, ST0);
-        step(plain, qt + 1, QU0, ST0, QU1, ST1);
-    }
-    if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
+    walk(std::false_type{});
+    if (workgroup_any(any_nan(accV) || any_nan(accK), QU0, wave)) walk(std::true_type{});
 
     if (krow < N) {
         uint16_t* vrow = dV + hoff + (size_t)krow * D;

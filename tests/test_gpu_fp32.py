@@ -95,3 +95,28 @@ def test_non_finite_inputs_reach_what_depends_on_them(gpa):
                 assert not torch.isfinite(dv[:row + 1, 3].float()).any()
                 assert not torch.isfinite(dq[row].float()).any()
                 assert torch.equal(dk[192:], base[4][0, 1, 192:])  # keys no such query sees
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_an_infinity_stays_one(gpa, d, causal, sign):
+    """P V and P^T dO with an infinite V or dO are infinite where P > 0, as an FP32
+    product is (zero BF16 parts of P must not make NaNs of them): rows outside the
+    infinity's own tile, where no masked probability meets it."""
+    N, row = 200, 70
+    g = torch.Generator().manual_seed(6)
+    x = [torch.randn(1, 2, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(4)]
+    # equal keys: uniform P, whose last two parts are 0 for a power of two of them
+    x[1][0, 1] = 0
+    base = _call(gpa, *x, causal, 0.125)
+    x[2][0, 1, row, 3] = sign * math.inf
+    _, o, lse, *_ = _call(gpa, *x, causal, 0.125)
+    assert (o[0, 1, 128 if causal else 0:, 3].float() == sign * math.inf).all()
+    keep = torch.arange(d, device="cuda") != 3
+    assert torch.equal(o[0, 1][:, keep], base[1][0, 1][:, keep]) and torch.equal(lse, base[2])
+    x[2][0, 1, row, 3] = 1.0
+    x[3][0, 1, row, 3] = sign * math.inf
+    _, o, lse, dq, dk, dv = _call(gpa, *x, causal, 0.125)
+    assert (dv[0, 1, :64 if causal else N, 3].float() == sign * math.inf).all()
+    assert torch.equal(dv[0, 1][:, keep], base[5][0, 1][:, keep])
