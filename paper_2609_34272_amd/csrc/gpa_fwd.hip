@@ -701,10 +701,9 @@ __global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 2 : GPA_FWD16_OCC) vo
 }
 
 // Takes the states of every row together, in split order, and finishes as the
-// kernels above do.  D/4 lanes share a row, 4 columns each: they read the row
-// maxima and sums of all splits at once into LDS, then all accumulators, so the pass
-// waits for two round trips to memory and not for two per split (about 4 us,
-// whatever S).  items [sequence][key/value head][chunk of rows].
+// kernels above do.  D/4 lanes share a row, 4 columns each: they read the
+// accumulators of all splits, and a split's row maximum and sum per lane, which LDS
+// hands round, before they wait once (about 4 us, whatever S).  items [sequence][key/value head][chunk of rows].
 template <int D>
 __global__ __launch_bounds__(256) void fwd_few_merge_kernel(
     const float* __restrict__ Oacc, const float* __restrict__ ML, uint16_t* __restrict__ O,
@@ -735,19 +734,24 @@ __global__ __launch_bounds__(256) void fwd_few_merge_kernel(
                          few_base(seq, sr.q0 - (size_t)kvh * G * total,
                                   sr.kv0 - (size_t)kvh * total_k, G) + r;
         static_assert(kFewMaxSplits <= LPR, "a lane per split");
-        if (have && j < S) {
-            M[rl][j] = ML[2 * (p + (size_t)j * rows)];
-            L[rl][j] = ML[2 * (p + (size_t)j * rows) + 1];
+        const bool mine = have && j < S;
+        const float mj = mine ? ML[2 * (p + (size_t)j * rows)] : 0.f;
+        const float lj = mine ? ML[2 * (p + (size_t)j * rows) + 1] : 0.f;
+        f32x4 x[kFewMaxSplits];
+#pragma unroll
+        for (int i = 0; i < kFewMaxSplits; ++i) {
+            x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (have && i < S)
+                x[i] = *reinterpret_cast<const f32x4*>(Oacc + (p + (size_t)i * rows) * D + col);
+        }
+        if (j < kFewMaxSplits) {
+            M[rl][j] = mj;
+            L[rl][j] = lj;
         }
         __syncthreads();
         if (have) {
             float m = -INFINITY, l = 0.f;
             f32x4 o = {0.f, 0.f, 0.f, 0.f};
-            f32x4 x[kFewMaxSplits];
-#pragma unroll
-            for (int i = 0; i < kFewMaxSplits; ++i)
-                if (i < S)
-                    x[i] = *reinterpret_cast<const f32x4*>(Oacc + (p + (size_t)i * rows) * D + col);
 #pragma unroll
             for (int i = 0; i < kFewMaxSplits; ++i) {
                 if (i >= S) break;
