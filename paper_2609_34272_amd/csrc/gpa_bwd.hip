@@ -165,7 +165,7 @@ void bwd_dq_kernel(
     int bh, tile;
     if constexpr (UNEVEN) {
         if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
+    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 2 : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     int bh, tile;
     if constexpr (UNEVEN) {
         if (!map_packed(blockIdx.x, BH, Hq, Nkmax, cu_k, total_k, false, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? snake_if_resident(2) : 0);
+    } else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? 2 : 0);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= Nk) return;  // a shorter sequence has no such tile

@@ -307,36 +307,42 @@ __device__ __forceinline__ float xor_sum(float v) {
 // end is heavy: the query-major causal kernels' last tiles do the most work,
 // the key-major kernels' first tiles do.
 //
-// snake_rounds: an XCD places its i-th workgroup on compute unit i mod 32
-// while it has free slots, so the first `resident` x 32 workgroups of an XCD
-// (resident = workgroups a unit holds) are placed before any finishes.
-// Reversing every other block of 32 of those positions (of 256 where heads are
-// not split over the XCDs) deals the heavy-first list out like a snake draft:
-// compute unit p gets list positions p, 63 - p, 64 + p, 127 - p, ..., about the
-// same total work on every unit.  This pays when the resident set holds most of
-// the grid (the d = 64 forward, 4 per unit, always; the other kernels that hold 2
-// where the grid is resident at once, snake_if_resident); later workgroups keep
-// the longest-first order, which the in-order dispatch balances by itself (with
-// 2 per unit and a grid of twice that the backward passes measured 5 % slower
-// with the snake).  Without and with it, us: forward 131 and 115 (4 heads of
-// 8192, d = 128), 36.5 and 32.4 (12 heads of 3000, d = 64); query pass 47.5 and
-// 42.7, key pass 56.2 and 51.0 (8 heads of 4096, d = 64).
+// resident: the workgroups that a compute unit holds (0: the order as it stands).
+// An XCD places its i-th workgroup on unit i mod 32 while it has free slots (i mod
+// 256 over the chip where heads are not split over the XCDs), so a grid of no more
+// rounds than that is placed before any workgroup finishes, and no later dispatch
+// evens the units out.  Its heavy-first list is dealt out like a snake draft: every
+// other round, counted from the last one, runs backwards over the units.  The last
+// round, which may be partial, then gives its few workgroups to the units that the
+// round before gave its lightest ones, and every unit has about the same total work.
+// beyond: in larger grids too, the first rounds; the forward and the FP32 baseline
+// at d = 64, whose 3 to 5 resident rounds are most of a grid.  In larger grids of the
+// others the longest-first order balances by itself (2 per unit and a grid of twice
+// that: 5 % slower with the snake), and the backward passes at d = 128 hold one.
+//
+// Heaviest first alone and with this, us: at d = 128 the forward of 4 heads of 4608,
+// 6144, 7680 and 8192 tokens 69.9, 94.4, 119.4 and 131 and 67.4, 91.0, 118.8 and 115,
+// 5 heads of 4160 71.0 and 63.8; at d = 64 query pass and key pass of 8 heads of
+// 2304, 3072, 3584 and 4096 tokens 26.9 + 31.0, 35.6 + 41.5, 41.5 + 49.1 and 47.5 +
+// 56.2 and 25.0 + 29.4, 31.8 + 37.9, 36.7 + 44.1 and 42.7 + 51.0, the forward of 5
+// heads of 4160 48.8 and 39.1.
 constexpr int kGroupTiles = 128;
 constexpr int kXcdCUs = 32;  // compute units per XCD
 __device__ __forceinline__ void map_block(int bid, int BH, int T, bool heavy_high, int* bh,
-                                          int* tile, int snake_rounds = 0) {
-    int heads = BH, base = 0, li = bid;
+                                          int* tile, int resident = 0, bool beyond = false) {
+    int heads = BH, base = 0, li = bid, units = 8 * kXcdCUs;
     if ((BH & 7) == 0) {
         heads = BH >> 3;
         base = (bid & 7) * heads;
         li = bid >> 3;
-        const int q = li / kXcdCUs, p = li - q * kXcdCUs;
-        if ((q & 1) && q < snake_rounds && q < (heads * T) / kXcdCUs)
-            li = q * kXcdCUs + (kXcdCUs - 1 - p);
-    } else if (snake_rounds > 0) {
-        constexpr int CUs = 8 * kXcdCUs;
-        const int q = li / CUs, p = li - q * CUs;
-        if ((q & 1) && q < snake_rounds && q < (heads * T) / CUs) li = q * CUs + (CUs - 1 - p);
+        units = kXcdCUs;
+    }
+    if (resident > 0) {
+        const int rounds = (heads * T + units - 1) / units;
+        const int q = li / units, p = li - q * units;
+        const bool back = rounds <= resident ? ((rounds - 1 - q) & 1) != 0
+                                             : beyond && (q & 1) && q < resident;
+        if (back) li = q * units + (units - 1 - p);
     }
     const int hg = min(heads, max(1, (kGroupTiles + T - 1) / T));
     const int group = li / (hg * T);
@@ -451,13 +457,6 @@ __device__ __forceinline__ bool map_packed(int bid, int BH, int Hq, int Nmax, co
     *bh = s * Hq + h;
     *tile = heavy_high ? lo - 1 : __builtin_amdgcn_readlane(Ts, s) - lo;
     return true;
-}
-
-// snake_rounds of map_block for a kernel that holds `rounds` workgroups per
-// compute unit: used where the whole grid is resident at once, so that no later
-// dispatch evens the units out.
-__device__ __forceinline__ int snake_if_resident(int rounds) {
-    return (int)gridDim.x <= rounds * 8 * kXcdCUs ? rounds : 0;
 }
 
 // Rows of one attention problem (a query head of one sequence) and its query

@@ -33,10 +33,10 @@
 // Work split: a workgroup has 4 waves and owns 64 rows (queries in the
 // forward and the query-major pass, keys in the key-major pass), 16 per wave;
 // it streams 64-row tiles of the other side through a double-buffered LDS
-// ring filled with the LDS DMA load.  At d = 64 a unit holds 4 workgroups of the
-// forward and the query pass and 3 of the key pass, so those rounds are dealt
-// out in snake order: 92 / 101 / 143 us without it and 89 / 94 / 140 with it (16
-// heads of 4096), 357 / 387 / 539 and 316 / 346 / 534 (16 of 8192); no
+// ring filled with the LDS DMA load.  At d = 64 a unit holds 5 workgroups of the
+// forward, 4 of the query pass and 3 of the key pass, and those rounds are dealt out
+// in snake order (map_block): without and with it, 92 / 101 / 143 us and 81 / 92 /
+// 137 us (16 heads of 4096), 82 / 77 / 115 and 66 / 55 / 83 (5 of 4160); no
 // difference at d = 128.
 #include "gpa_device.h"
 #include "gpa_launch.h"
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 4 : 0);
+    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 5 : 0, true);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t KV1[2][kTile * D];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 4 : 0);
+    map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 4 : 0, true);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
     __shared__ __attribute__((aligned(16))) float ST1[kF32Stat];
     const int T = (N + kTile - 1) / kTile;
     int bh, tile;
-    map_block(blockIdx.x, BH, T, false, &bh, &tile, D == 64 ? 3 : 0);
+    map_block(blockIdx.x, BH, T, false, &bh, &tile, D == 64 ? 3 : 0, true);
     const size_t hoff = (size_t)bh * N * D;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

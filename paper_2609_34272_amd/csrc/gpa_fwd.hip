@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 1 : GPA_FWD_OCC) void
     int bh, tile;
     if constexpr (UNEVEN) {
         if (!map_packed(bid, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(bid, BH, T, causal != 0, &bh, &tile, snake_if_resident(2));
+    } else map_block(bid, BH, T, causal != 0, &bh, &tile, 2);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 2 : GPA_FWD16_OCC) vo
     int bh, tile;
     if constexpr (UNEVEN) {
         if (!map_packed(bid, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(bid, BH, T, causal != 0, &bh, &tile, GPA_FWD16_OCC);
+    } else map_block(bid, BH, T, causal != 0, &bh, &tile, 5, true);
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile

@@ -402,11 +402,14 @@ def test_few_queries_on_long_keys(gpa, newq, Hq, Hkv, d, causal):
             assert (ho - o1[h, a:b].double().cpu()).norm() <= 5e-3 * e.norm()
 
 
-@pytest.mark.parametrize("H,N,d", [(3, 1000, 128), (5, 4160, 64), (8, 4096, 64), (4, 8192, 128), (12, 2700, 64)])
+@pytest.mark.parametrize("H,N,d", [(3, 1000, 128), (5, 4160, 64), (8, 4096, 64), (4, 8192, 128), (12, 2700, 64),
+                                   (5, 4160, 128), (8, 2304, 128), (8, 2305, 64), (16, 1600, 64), (12, 5000, 64)])
 def test_resident_grid_order_covers_every_tile(gpa, H, N, d):
     """Grids that are resident at once take their tiles in snake order, in rounds
     of 256 workgroups (or of 32 per XCD): each head still equals that head run
-    alone, bit for bit, at sizes with a partial last round."""
+    alone, bit for bit, at sizes with a partial last round.  At d = 64 all three
+    passes are reordered (two rounds in 5 x 4160, 8 x 2305, 16 x 1600; the forward
+    also in three and four), at d = 128 the forward."""
     g = torch.Generator().manual_seed(N)
     q, k, v, u = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(4))
 
@@ -419,3 +422,15 @@ def test_resident_grid_order_covers_every_tile(gpa, H, N, d):
         for n, w, p in zip(("O", "LSE", "dQ", "dK", "dV"), whole,
                            run([t[:, h:h + 1].contiguous() for t in (q, k, v, u)])):
             assert torch.equal(w[:, h:h + 1], p), (n, h)
+
+
+@pytest.mark.parametrize("H,N", [(5, 4160), (8, 2305), (16, 2500)])
+def test_fp32_resident_grid_order_covers_every_tile(gpa, H, N):
+    """The same for the FP32 baseline's passes at d = 64 (two and three rounds)."""
+    g = torch.Generator().manual_seed(N)
+    x = [torch.randn(1, H, N, 64, generator=g).to(torch.bfloat16).cuda() for _ in range(4)]
+    whole = gpa.fp32_attn(*x, True)
+    for h in (0, H // 2, H - 1):
+        alone = gpa.fp32_attn(*[t[:, h:h + 1].contiguous() for t in x], True)
+        for n, w, a in zip(("O", "LSE", "dQ", "dK", "dV"), whole, alone):
+            assert torch.equal(w[:, h:h + 1], a), (n, h)
