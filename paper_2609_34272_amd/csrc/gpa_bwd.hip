@@ -154,8 +154,8 @@ void bwd_dq_kernel(
     constexpr int QG = 4 / NB;
     constexpr int NTHR = 64 * 2 * QG;
     // A three-slot ring of [K tile, V tile] (row-major, swizzled): while tile
-    // i is computed on, tiles i+1 and i+2 are in flight.  Slot 0 is reused at
-    // the end for the pairwise reduction.
+    // i is computed on, tiles i+1 and i+2 are in flight.  The slots are reused at
+    // the end for the pairwise exchange.
     constexpr int TILE_E = kTile * D;
     __shared__ __attribute__((aligned(16))) uint16_t S0[2 * TILE_E];
     __shared__ __attribute__((aligned(16))) uint16_t S1[2 * TILE_E];
@@ -349,7 +349,7 @@ void bwd_dq_kernel(
         else
             step(masked, kt, S2, S1);
     }
-    // The zero fills issued by the last steps must land before slot 0 is
+    // The zero fills issued by the last steps must land before the slots are
     // reused for the reduction.
     wait_vm_lgkm0<0>();
     __builtin_amdgcn_s_barrier();
@@ -870,16 +870,19 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     // A key tile that no query sees (qt0 >= T) takes no step and stores zeros.
     if (qt0 < T) step(masked, qt0, B0, B2);
     if (qt0 + 1 < T) step(masked, qt0 + 1, B1, B0);
-    // Pin where the loop's code starts, 16 bytes into a 32-byte window: the same
-    // instructions run 86 us there and 89, 88 and 86 us at 0, 8 and 24 bytes
-    // (h16_n4096_d64 gproj); without this, any edit before the loop moves it.
-    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    // Pin where the loop's code starts: at 0, 4, ..., 28 bytes into a 32-byte window
+    // the same instructions take 91, 92, 90, 89, 87, 87, 86.5 and 88.5 us
+    // (h16_n4096_d64) and 1214, 1216, 1200, 1189, 1182, 1183, 1182 and 1192
+    // (h16_n16384_d64), and without a pin any edit before the loop moves it.  The
+    // other instantiations (plain, d = 128) take the same time wherever it starts.
+    if constexpr (D == 64 && GPROJ && !FUSED_DQ)
+        asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int qt = qt0 + 2; qt < T; qt += 3) {
         step(plain, qt, B2, B1);
         if (qt + 1 < T) step(plain, qt + 1, B0, B2);
         if (qt + 2 < T) step(plain, qt + 2, B1, B0);
     }
-    // The zero fills issued by the last steps must land before B0 is reused
+    // The zero fills issued by the last steps must land before B0 and B1 are reused
     // for the reduction.
     wait_vm_lgkm0<0>();
     __builtin_amdgcn_s_barrier();
