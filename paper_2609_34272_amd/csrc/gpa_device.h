@@ -210,6 +210,18 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
     __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | ((VM >> 4) << 14));
 }
 
+// Where control flow parts or meets right behind matrix products.  A vector
+// instruction may touch the registers of a 16x16x32 product eight wait states after
+// it at the earliest; the compiler keeps that within a block, but over an edge it has
+// been seen to count a branch that is not on the path, and to copy or overwrite them
+// one or two states too early (with wrong values in one kernel).  No instruction moves
+// over this, and the eight states pass here.
+__device__ __forceinline__ void mfma_settle() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Transposed MFMA operand read straight from a row-major LDS tile X[k][n]
 // with the gfx950 LDS transpose load ds_read_b64_tr_b16.  Within each 16-lane
 // group, that instruction hands lane j element j of the 4 x 16 block formed by

@@ -247,11 +247,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
             tr_accumulate<D, decltype(exact_inf)::value>(Vc, s, acc, c16, g);
+            if constexpr (decltype(exact_inf)::value) mfma_settle();
             wait_vm_lgkm0<0>();
             __syncthreads();
         };
         const std::false_type plain;
         const std::true_type masked;
+        // Two steps a turn, each with its buffers: the accumulators then stay where they
+        // are over the loop's edge, and no copy of them can come too early (mfma_settle).
         int kt = 0;
         for (; kt + 1 < nplain; kt += 2) {
             step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
@@ -269,6 +272,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
         }
     };
     walk(std::false_type{});
+    mfma_settle();
     if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
 
     const float l = xor_sum(lrun);
@@ -379,11 +383,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
                 }
             }
             tr_accumulate<D, decltype(exact_inf)::value>(Kc, ds, acc, c16, g);
+            if constexpr (decltype(exact_inf)::value) mfma_settle();
             wait_vm_lgkm0<0>();
             __syncthreads();
         };
         const std::false_type plain;
         const std::true_type masked;
+        // Two steps a turn, each with its buffers: the accumulators then stay where they
+        // are over the loop's edge, and no copy of them can come too early (mfma_settle).
         int kt = 0;
         for (; kt + 1 < nplain; kt += 2) {
             step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
@@ -401,6 +408,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
         }
     };
     walk(std::false_type{});
+    mfma_settle();
     if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
 
     if (qok) {
@@ -503,6 +511,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
             }
             tr_accumulate<D, decltype(exact_inf)::value>(Uc, p, accV, c16, g);
             tr_accumulate<D, decltype(exact_inf)::value>(Qc, ds, accK, c16, g);
+            if constexpr (decltype(exact_inf)::value) mfma_settle();
             wait_vm_lgkm0<0>();
             __syncthreads();
         };
@@ -518,6 +527,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
             step(plain, qt, QU0, ST0, QU1, ST1);
             ++qt;
         }
+        // two steps a turn, as in the passes above
         for (; qt + 1 < T; qt += 2) {
             step(plain, qt, QU1, ST1, QU0, ST0);
             step(plain, qt + 1, QU0, ST0, QU1, ST1);
@@ -525,6 +535,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
         if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
     };
     walk(std::false_type{});
+    mfma_settle();
     if (workgroup_any(any_nan(accV) || any_nan(accK), QU0, wave)) walk(std::true_type{});
 
     if (krow < N) {

@@ -207,6 +207,7 @@ __device__ __forceinline__ void few_rows(
                     for (int j = 0; j < 2; ++j)
                         acc[mb] = mfma_16x16x32(ld_tr_operand<D>(Vc, 32 * j, mb * 16, c16, g), pf[j],
                                                 acc[mb]);
+                mfma_settle();
             };
             auto step = [&](int kt, const uint16_t (&KV)[2][kTile * D],
                             uint16_t (&next)[2][kTile * D]) {
@@ -444,6 +445,7 @@ __global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 1 : GPA_FWD_OCC) void
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) acc[nb][mb] = mfma_16x16x32(va, pf[nb], acc[nb][mb]);
         }
+        if constexpr (MASK) mfma_settle();  // the loop over these steps copies acc
         __builtin_amdgcn_s_waitcnt(0);  // this wave's loads of the next tile
         __syncthreads();
     };
@@ -655,6 +657,7 @@ __global__ __launch_bounds__(kThreads, FEW == Few::kWalk ? 2 : GPA_FWD16_OCC) vo
             for (int j = 0; j < 2; ++j)
                 acc[mb] = mfma_16x16x32(ld_tr_operand<D>(Vc, 32 * j, mb * 16, c16, g), pf[j],
                                         acc[mb]);
+        if constexpr (MASK) mfma_settle();  // the loop over these steps copies acc
         wait_vm_lgkm0<0>();
         __builtin_amdgcn_s_barrier();
     };
