@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gpa_launch.h"
+
 namespace gpa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -394,7 +396,6 @@ __device__ __forceinline__ void map_block(int bid, int BH, int T, bool heavy_hig
 // and one of 8000, 32 heads: 25.0, 24.0 and 24.3 ms (37.9 in one group, where
 // every head's K and V stream at once and miss in L2).
 constexpr int kPackedTiles = 512;
-constexpr int kPackedCompact = 64;
 
 // Sum over the 64 lanes, in every lane: rotations within the rows of 16 lanes,
 // then the row and half swaps of xor_sum.

@@ -118,14 +118,17 @@ inline bool may_have_few(const Shape& s) {
     return s.cu != nullptr && s.cu_k != s.cu && s.Nk >= kFewKeys;
 }
 
+// Sequences that the kernels of uneven packs search among for their tile: one per
+// lane of a wave.
+constexpr int kPackedCompact = 64;
+
 // Workgroups of the UNEVEN instantiations for one side: one place per tile (a
-// run's last tile may be partial) and head, or, with more sequences than the
-// kernels search among (kPackedCompact, 64), as many places for every sequence
-// as for the longest.
+// run's last tile may be partial) and head, or, with more than kPackedCompact
+// sequences, as many places for every sequence as for the longest.
 inline unsigned packed_grid(const Shape& s, int total, int longest) {
     const int64_t nseq = s.BH / s.Hq, T = (longest + 63) / 64;
     int64_t places = nseq * T;
-    if (nseq <= 64 && total / 64 + nseq < places) places = total / 64 + nseq;
+    if (nseq <= kPackedCompact && total / 64 + nseq < places) places = total / 64 + nseq;
     return (unsigned)(places * s.Hq);
 }
 
