@@ -163,10 +163,12 @@ void bwd_dq_kernel(
 
     const int T = (Nmax + kTile - 1) / kTile;  // tiles of the longest problem
     int bh, tile;
-    offsets_early(cu, cu_k);
     if constexpr (UNEVEN) {
         if (!map_packed(blockIdx.x, BH, Hq, Nmax, cu, total, causal != 0, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 2 : 0);
+    } else {
+        offsets_early(cu, cu_k);
+        map_block(blockIdx.x, BH, T, causal != 0, &bh, &tile, D == 64 ? 2 : 0);
+    }
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= N) return;  // a shorter sequence has no such tile
@@ -535,10 +537,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? GPA_DKDV_OCC64 : 1) void bwd_dk
     const int Tq = (Nmax + kTile - 1) / kTile;   // query tiles of the longest problem
     const int Tk = (Nkmax + kTile - 1) / kTile;  // key tiles of the longest problem
     int bh, tile;
-    offsets_early(cu, cu_k);
     if constexpr (UNEVEN) {
         if (!map_packed(blockIdx.x, BH, Hq, Nkmax, cu_k, total_k, false, &bh, &tile)) return;
-    } else map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? 2 : 0);
+    } else {
+        offsets_early(cu, cu_k);
+        map_block(blockIdx.x, BH, Tk, false, &bh, &tile, D == 64 ? 2 : 0);
+    }
     const SeqRows sr = seq_rows(cu, cu_k, bh, Nmax, Nkmax, G, Hq, total, total_k);
     const int N = sr.nq, Nk = sr.nk;
     if (tile * kTile >= Nk) return;  // a shorter sequence has no such tile

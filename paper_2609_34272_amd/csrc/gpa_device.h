@@ -472,7 +472,8 @@ __device__ __forceinline__ bool map_packed(int bid, int BH, int Hq, int Nmax, co
 
 // Asks for the offsets' pointers with the first kernel arguments.  Left alone, the
 // compiler may load them only where seq_rows reads them, one more trip to memory in
-// front of everything else (0.3 to 0.4 us of a pass).
+// front of everything else (0.3 to 0.4 us of a pass).  Uneven packs need them first
+// anyway (and the query pass of 12 sequences, d = 128, was 2 % slower with this).
 __device__ __forceinline__ void offsets_early(const int* cu, const int* cu_k) {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("" : : "s"(cu), "s"(cu_k));

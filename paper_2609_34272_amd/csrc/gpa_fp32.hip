@@ -84,9 +84,6 @@ struct Split {
 __device__ __forceinline__ bool is_finite(float x) {
     return (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u;
 }
-__device__ __forceinline__ bool is_nan(float x) {
-    return (__float_as_uint(x) & 0x7FFFFFFFu) > 0x7F800000u;
-}
 __device__ __forceinline__ float upper(float x) {
     return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
 }
@@ -120,7 +117,7 @@ __device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
 //
 // A factor whose mid or lo part is 0 turns an infinity of X into a NaN, and so does
 // an infinite factor.  A pass that ends with a NaN in its accumulators therefore
-// runs again with EXACT_INF (any_nan): values of X that are not finite then meet the
+// runs again with EXACT_INF (nan_sum): values of X that are not finite then meet the
 // hi part alone, which has the factor's sign and is 0 where it is, so the products
 // are the infinities and NaNs of one FP32 product, and all others what they were.
 template <int D, bool EXACT_INF>
@@ -143,24 +140,24 @@ __device__ __forceinline__ void tr_accumulate(const uint16_t* X, const f32x4 (&b
     }
 }
 
+// A sum of accumulators that is a NaN if one of them is (or if infinities or an
+// overflow meet, for which the second walk is merely superfluous).
 template <int MB>
-__device__ __forceinline__ bool any_nan(const f32x4 (&acc)[MB]) {
-    bool nan = false;
+__device__ __forceinline__ float nan_sum(const f32x4 (&acc)[MB]) {
+    f32x4 t = acc[0];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) nan |= is_nan(acc[mb][i]);
-    return nan;
+    for (int mb = 1; mb < MB; ++mb) t += acc[mb];
+    return (t[0] + t[1]) + (t[2] + t[3]);
 }
-// Whether x holds in any lane of the workgroup.  `lds`: a word per wave, free.
-__device__ __forceinline__ bool workgroup_any(bool x, void* lds, int wave) {
-    volatile int* w = reinterpret_cast<volatile int*>(lds);
-    const bool any = __builtin_amdgcn_ballot_w64(x) != 0;
-    if ((threadIdx.x & 63) == 0) w[wave] = any;
+// Whether x is a NaN in any lane of the workgroup.  `lds`: four words that nothing
+// uses until the next barrier.
+__device__ __forceinline__ bool workgroup_nan(float x, void* lds, int wave) {
+    typedef int i32x4_t __attribute__((ext_vector_type(4)));
+    const bool any = __builtin_amdgcn_ballot_w64((__float_as_uint(x) & 0x7FFFFFFFu) > 0x7F800000u) != 0;
+    if ((threadIdx.x & 63) == 0) reinterpret_cast<int*>(lds)[wave] = any;
     __syncthreads();
-    const bool all = (w[0] | w[1] | w[2] | w[3]) != 0;
-    __syncthreads();
-    return all;
+    const i32x4_t w = *reinterpret_cast<const i32x4_t*>(lds);
+    return (w[0] | w[1] | w[2] | w[3]) != 0;
 }
 
 // ------------------------------------------------------------------ forward
@@ -273,7 +270,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
     };
     walk(std::false_type{});
     mfma_settle();
-    if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
+    if (workgroup_nan(nan_sum(acc), KV0, wave)) {
+        __syncthreads();
+        walk(std::true_type{});
+    }
 
     const float l = xor_sum(lrun);
     if (qrow < N) {
@@ -409,7 +409,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
     };
     walk(std::false_type{});
     mfma_settle();
-    if (workgroup_any(any_nan(acc), KV0, wave)) walk(std::true_type{});
+    if (workgroup_nan(nan_sum(acc), KV0, wave)) {
+        __syncthreads();
+        walk(std::true_type{});
+    }
 
     if (qok) {
         uint16_t* drow = dQ + hoff + (size_t)qrow * D;
@@ -536,7 +539,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
     };
     walk(std::false_type{});
     mfma_settle();
-    if (workgroup_any(any_nan(accV) || any_nan(accK), QU0, wave)) walk(std::true_type{});
+    if (workgroup_nan(nan_sum(accV) + nan_sum(accK), QU0, wave)) {
+        __syncthreads();
+        walk(std::true_type{});
+    }
 
     if (krow < N) {
         uint16_t* vrow = dV + hoff + (size_t)krow * D;
