@@ -20,8 +20,8 @@
 // bias 0 to 64; LSE 3.0e-8 to 4.3e-8 (3.1e-8 to 4.9e-8).  What bounds the
 // kernels now is the vector ALU (the split is 5.5 instructions per pair and FP32
 // factor, of 11 to 20): forward / query pass / key pass 369 / 537 / 659 us on the
-// FP32 matrix cores, 85 / 90 / 134 us here (16 heads of 4096 causal tokens, d =
-// 64; 1552 and 307 us in all).
+// FP32 matrix cores, 80 / 91 / 135 us here (16 heads of 4096 causal tokens, d =
+// 64; 1552 and 306 us in all).
 //
 // MFMA layouts as in the BF16 kernels (16x16x32, wave64): lane (c16 = lane & 15,
 // g = lane >> 4) supplies 8 values along k of row (A) or column (B) c16; the
@@ -35,8 +35,8 @@
 // it streams 64-row tiles of the other side through a double-buffered LDS
 // ring filled with the LDS DMA load.  At d = 64 a unit holds 5 workgroups of the
 // forward, 4 of the query pass and 3 of the key pass, and those rounds are dealt out
-// in snake order (map_block): without and with it, 92 / 101 / 143 us and 81 / 92 /
-// 137 us (16 heads of 4096), 82 / 77 / 115 and 66 / 55 / 83 (5 of 4160); no
+// in snake order (map_block): without and with it, 92 / 101 / 143 us and 80 / 91 /
+// 135 us (16 heads of 4096), 82 / 77 / 115 and 66 / 55 / 83 (5 of 4160); no
 // difference at d = 128.
 #include "gpa_device.h"
 #include "gpa_launch.h"

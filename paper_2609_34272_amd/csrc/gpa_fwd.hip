@@ -42,8 +42,8 @@ __device__ __forceinline__ float exp_arg(float x, float m, float c) {
 }
 
 // How a forward kernel takes the packed sequences that few_sequence (gpa_launch.h)
-// names: not apart from the others, by splits that leave their states in a
-// workspace, or by splits one after the other.
+// names: like the others (kNone), by splits of their keys that leave their states in a
+// workspace (kSplit), or by the same splits one after the other (kWalk).
 enum class Few { kNone, kSplit, kWalk };
 struct FewArgs {
     float* Oacc = nullptr;  // states: FP32 O^T accumulators [Hkv, rows, D],
