@@ -59,7 +59,9 @@ typedef __attribute__((address_space(3))) bf16v4_t lds_bf16v4_t;
 // and rows of equal parity have to differ: bits 1-2) above row bit 3, with the
 // top of them inverted in rows 8-15: rows 8-11 then pair with rows 4-7.  Without
 // that inversion the 16-byte reads conflict two ways (SQ_LDS_BANK_CONFLICT 25 to
-// 40 % of the LDS cycles); with it the counter reads 0 in every kernel.  Measured
+// 40 % of the LDS cycles); with it the counter reads 0 in every kernel (0.2 to 0.5
+// cycles an instruction in the atomic schedule's key pass, whose exchange tiles are
+// its own).  Measured
 // before and after, us: d = 128 query pass 145 and 138, key pass 181 and 173
 // (h16_n4096_d128, gproj); 8560 and 8070, 10920 and 10660 (b8_h32_n8192_d128);
 // d = 64 forward 667 and 655, query pass 932 and 920 (h16_n16384_d64); the FP32
