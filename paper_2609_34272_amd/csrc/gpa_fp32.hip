@@ -116,10 +116,10 @@ __device__ __forceinline__ Split split3(const f32x4& x0, const f32x4& x1) {
 // c16] and X[32 kb2 + 16 + 4 g + r][...] for r = 0..3.
 //
 // A factor whose mid or lo part is 0 turns an infinity of X into a NaN, and so does
-// an infinite factor.  A pass that ends with a NaN in its accumulators therefore
-// runs again with EXACT_INF (nan_sum): values of X that are not finite then meet the
-// hi part alone, which has the factor's sign and is 0 where it is, so the products
-// are the infinities and NaNs of one FP32 product, and all others what they were.
+// an infinite factor.  A wave that ends with a NaN in its accumulators therefore
+// forms them again with EXACT_INF: values of X that are not finite then meet the hi
+// part alone, which has the factor's sign and is 0 where it is, so the products are
+// the infinities and NaNs of one FP32 product, and all others what they were.
 template <int D, bool EXACT_INF>
 __device__ __forceinline__ void tr_accumulate(const uint16_t* X, const f32x4 (&b)[4],
                                               f32x4 (&acc)[D / 16], int c16, int g) {
@@ -140,8 +140,8 @@ __device__ __forceinline__ void tr_accumulate(const uint16_t* X, const f32x4 (&b
     }
 }
 
-// A sum of accumulators that is a NaN if one of them is (or if infinities or an
-// overflow meet, for which the second walk is merely superfluous).
+// Whether an accumulator of the wave may be a NaN: their sum is one then (and where
+// infinities or an overflow meet, for which the second walk is merely superfluous).
 template <int MB>
 __device__ __forceinline__ float nan_sum(const f32x4 (&acc)[MB]) {
     f32x4 t = acc[0];
@@ -149,15 +149,21 @@ __device__ __forceinline__ float nan_sum(const f32x4 (&acc)[MB]) {
     for (int mb = 1; mb < MB; ++mb) t += acc[mb];
     return (t[0] + t[1]) + (t[2] + t[3]);
 }
-// Whether x is a NaN in any lane of the workgroup.  `lds`: four words that nothing
-// uses until the next barrier.
-__device__ __forceinline__ bool workgroup_nan(float x, void* lds, int wave) {
-    typedef int i32x4_t __attribute__((ext_vector_type(4)));
-    const bool any = __builtin_amdgcn_ballot_w64((__float_as_uint(x) & 0x7FFFFFFFu) > 0x7F800000u) != 0;
-    if ((threadIdx.x & 63) == 0) reinterpret_cast<int*>(lds)[wave] = any;
-    __syncthreads();
-    const i32x4_t w = *reinterpret_cast<const i32x4_t*>(lds);
-    return (w[0] | w[1] | w[2] | w[3]) != 0;
+__device__ __forceinline__ bool wave_nan(float x) {
+    return __builtin_amdgcn_ballot_w64((__float_as_uint(x) & 0x7FFFFFFFu) > 0x7F800000u) != 0;
+}
+
+// Stages a tile for one wave alone, which has the LDS tile `dst` to itself: what it
+// read there before has arrived, and the tile is there on return.
+template <int D>
+__device__ __forceinline__ void stage_alone(int lane, const uint16_t* head, uint16_t* dst, int row0,
+                                            int N) {
+    asm volatile("" : "+v"(lane));  // the offsets are formed here, and kept nowhere
+    TileDma<D, 64> dma;
+    dma.init(lane, 0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    dma.load(head, dst, row0, N);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
 // ------------------------------------------------------------------ forward
@@ -186,93 +192,103 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 5 : 2) void f32_fwd_kernel(
     const KeyRange kr = key_range(tile, N, 0, causal);
     const int nkv = kr.nkv, nplain = kr.nplain;
     const float lg = kLog2e;
-    float mrun, lrun;  // scaled running maximum; this lane's share of l
+    float mrun = -INFINITY, lrun = 0.f;  // scaled running maximum; this lane's share of l
     f32x4 acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     TileDma<D> dma;
     dma.init(lane, wave);
+    dma.load(K + hoff, KV0[0], 0, N);
+    dma.load(V + hoff, KV0[1], 0, N);
+    wait_vm_lgkm0<0>();
+    __syncthreads();
 
-    auto walk = [&](auto exact_inf) {
+    // P of tile kt into s, with the running maximum and sum and the rescaled output
+    auto probs = [&](auto masked, int kt, const uint16_t* Kc, f32x4 (&s)[4]) {
+        constexpr bool MASK = decltype(masked)::value;
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            s[kb] = block_dot<D>(Kc, 16 * kb, qf, c16, g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float v = scale * s[kb][i];
+                if constexpr (MASK) {
+                    const int key = kt * kTile + 16 * kb + 4 * g + i;
+                    v = (key < N && (!causal || key <= qrow)) ? v : -INFINITY;
+                }
+                s[kb][i] = v;
+                tmax = fmaxf(tmax, v);
+            }
+        }
+        const float mnew = fmaxf(mrun, xor_max(tmax));
+        // a row that has seen no key yet keeps m = -inf; its factors are 1, 0
+        const float corr = mnew == -INFINITY ? 1.f : fexp2((mrun - mnew) * lg);
+        const float msub = mnew == -INFINITY ? 0.f : mnew;
+        mrun = mnew;
+        float lsum = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float p = fexp2((s[kb][i] - msub) * lg);
+                s[kb][i] = p;
+                lsum += p;
+            }
+        lrun = lrun * corr + lsum;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
+    };
+    auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
+                    uint16_t* Vn) {
+        if (kt + 1 < nkv) {
+            dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
+            dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 s[4];
+        probs(masked, kt, Kc, s);
+        tr_accumulate<D, false>(Vc, s, acc, c16, g);
+        wait_vm_lgkm0<0>();
+        __syncthreads();
+    };
+    const std::false_type plain;
+    const std::true_type masked;
+    // Two steps a turn, each with its buffers: the accumulators then stay where they
+    // are over the loop's edge, and no copy of them can come too early (mfma_settle).
+    int kt = 0;
+    for (; kt + 1 < nplain; kt += 2) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+    }
+    if (kt < nplain) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        ++kt;
+    }
+    // Tile kt lives in buffer kt mod 2.
+    // At most one tile needs masks: the diagonal one, or the key tail.
+    if (kt < nkv) {
+        if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
+        else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+    }
+    mfma_settle();
+    if (__builtin_expect(wave_nan(nan_sum(acc)), 0)) {
+        // again with EXACT_INF, this wave alone: each wave has one of the four tiles
+        uint16_t* buf = wave < 2 ? KV0[wave] : KV1[wave - 2];
         mrun = -INFINITY;
         lrun = 0.f;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        dma.load(K + hoff, KV0[0], 0, N);
-        dma.load(V + hoff, KV0[1], 0, N);
-        wait_vm_lgkm0<0>();
-        __syncthreads();
-
-        auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
-                        uint16_t* Vn) {
-            constexpr bool MASK = decltype(masked)::value;
-            if (kt + 1 < nkv) {
-                dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
-                dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+        for (int t = 0; t < nkv; ++t) {
             f32x4 s[4];
-            float tmax = -INFINITY;
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                s[kb] = block_dot<D>(Kc, 16 * kb, qf, c16, g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float v = scale * s[kb][i];
-                    if constexpr (MASK) {
-                        const int key = kt * kTile + 16 * kb + 4 * g + i;
-                        v = (key < N && (!causal || key <= qrow)) ? v : -INFINITY;
-                    }
-                    s[kb][i] = v;
-                    tmax = fmaxf(tmax, v);
-                }
-            }
-            const float mnew = fmaxf(mrun, xor_max(tmax));
-            // a row that has seen no key yet keeps m = -inf; its factors are 1, 0
-            const float corr = mnew == -INFINITY ? 1.f : fexp2((mrun - mnew) * lg);
-            const float msub = mnew == -INFINITY ? 0.f : mnew;
-            mrun = mnew;
-            float lsum = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float p = fexp2((s[kb][i] - msub) * lg);
-                    s[kb][i] = p;
-                    lsum += p;
-                }
-            lrun = lrun * corr + lsum;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[mb] *= corr;
-            tr_accumulate<D, decltype(exact_inf)::value>(Vc, s, acc, c16, g);
-            if constexpr (decltype(exact_inf)::value) mfma_settle();
-            wait_vm_lgkm0<0>();
-            __syncthreads();
-        };
-        const std::false_type plain;
-        const std::true_type masked;
-        // Two steps a turn, each with its buffers: the accumulators then stay where they
-        // are over the loop's edge, and no copy of them can come too early (mfma_settle).
-        int kt = 0;
-        for (; kt + 1 < nplain; kt += 2) {
-            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-            step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+            stage_alone<D>(lane, K + hoff, buf, t * kTile, N);
+            probs(masked, t, buf, s);
+            stage_alone<D>(lane, V + hoff, buf, t * kTile, N);
+            tr_accumulate<D, true>(buf, s, acc, c16, g);
+            mfma_settle();
         }
-        if (kt < nplain) {
-            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-            ++kt;
-        }
-        // Tile kt lives in buffer kt mod 2.
-        // At most one tile needs masks: the diagonal one, or the key tail.
-        if (kt < nkv) {
-            if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-            else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-        }
-    };
-    walk(std::false_type{});
-    mfma_settle();
-    if (workgroup_nan(nan_sum(acc), KV0, wave)) {
-        __syncthreads();
-        walk(std::true_type{});
     }
 
     const float l = xor_sum(lrun);
@@ -346,72 +362,90 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void f32_dq_kernel(
     const KeyRange kr = key_range(tile, N, 0, causal);
     const int nkv = kr.nkv, nplain = kr.nplain;
     f32x4 acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     TileDma<D> dma;
     dma.init(lane, wave);
     wait_vm_lgkm0<0>();
-    auto walk = [&](auto exact_inf) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        dma.load(K + hoff, KV0[0], 0, N);
-        dma.load(V + hoff, KV0[1], 0, N);
-        wait_vm_lgkm0<0>();
-        __syncthreads();
+    dma.load(K + hoff, KV0[0], 0, N);
+    dma.load(V + hoff, KV0[1], 0, N);
+    wait_vm_lgkm0<0>();
+    __syncthreads();
 
-        auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
-                        uint16_t* Vn) {
-            constexpr bool MASK = decltype(masked)::value;
-            if (kt + 1 < nkv) {
-                dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
-                dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            f32x4 ds[4];
+    // dS of key block kb of tile kt from its S and dP
+    auto grads = [&](auto masked, int kt, int kb, const f32x4& s, const f32x4& dp, f32x4& ds) {
+        constexpr bool MASK = decltype(masked)::value;
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const f32x4 s = block_dot<D>(Kc, 16 * kb, qf, c16, g);
-                const f32x4 dp = block_dot<D>(Vc, 16 * kb, uf, c16, g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float p = fexp2((scale * s[i] - mi) * lg) * li;
-                    if constexpr (MASK) {
-                        const int key = kt * kTile + 16 * kb + 4 * g + i;
-                        p = (key < N && (!causal || key <= qrow)) ? p : 0.f;
-                    }
-                    ds[kb][i] = p * (dp[i] - Di);
-                    if constexpr (MASK) ds[kb][i] = p != 0.f ? ds[kb][i] : 0.f;
-                }
+        for (int i = 0; i < 4; ++i) {
+            float p = fexp2((scale * s[i] - mi) * lg) * li;
+            if constexpr (MASK) {
+                const int key = kt * kTile + 16 * kb + 4 * g + i;
+                p = (key < N && (!causal || key <= qrow)) ? p : 0.f;
             }
-            tr_accumulate<D, decltype(exact_inf)::value>(Kc, ds, acc, c16, g);
-            if constexpr (decltype(exact_inf)::value) mfma_settle();
-            wait_vm_lgkm0<0>();
-            __syncthreads();
-        };
-        const std::false_type plain;
-        const std::true_type masked;
-        // Two steps a turn, each with its buffers: the accumulators then stay where they
-        // are over the loop's edge, and no copy of them can come too early (mfma_settle).
-        int kt = 0;
-        for (; kt + 1 < nplain; kt += 2) {
-            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-            step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
-        }
-        if (kt < nplain) {
-            step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
-            ++kt;
-        }
-        // Tile kt lives in buffer kt mod 2.
-        // At most one tile needs masks: the diagonal one, or the key tail.
-        if (kt < nkv) {
-            if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
-            else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+            ds[i] = p * (dp[i] - Di);
+            if constexpr (MASK) ds[i] = p != 0.f ? ds[i] : 0.f;
         }
     };
-    walk(std::false_type{});
-    mfma_settle();
-    if (workgroup_nan(nan_sum(acc), KV0, wave)) {
+    auto step = [&](auto masked, int kt, const uint16_t* Kc, const uint16_t* Vc, uint16_t* Kn,
+                    uint16_t* Vn) {
+        if (kt + 1 < nkv) {
+            dma.load(K + hoff, Kn, (kt + 1) * kTile, N);
+            dma.load(V + hoff, Vn, (kt + 1) * kTile, N);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 ds[4];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            const f32x4 s = block_dot<D>(Kc, 16 * kb, qf, c16, g);
+            const f32x4 dp = block_dot<D>(Vc, 16 * kb, uf, c16, g);
+            grads(masked, kt, kb, s, dp, ds[kb]);
+        }
+        tr_accumulate<D, false>(Kc, ds, acc, c16, g);
+        wait_vm_lgkm0<0>();
         __syncthreads();
-        walk(std::true_type{});
+    };
+    const std::false_type plain;
+    const std::true_type masked;
+    // Two steps a turn, each with its buffers: the accumulators then stay where they
+    // are over the loop's edge, and no copy of them can come too early (mfma_settle).
+    int kt = 0;
+    for (; kt + 1 < nplain; kt += 2) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        step(plain, kt + 1, KV1[0], KV1[1], KV0[0], KV0[1]);
+    }
+    if (kt < nplain) {
+        step(plain, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+        ++kt;
+    }
+    // Tile kt lives in buffer kt mod 2.
+    // At most one tile needs masks: the diagonal one, or the key tail.
+    if (kt < nkv) {
+        if (kt & 1) step(masked, kt, KV1[0], KV1[1], KV0[0], KV0[1]);
+        else step(masked, kt, KV0[0], KV0[1], KV1[0], KV1[1]);
+    }
+    mfma_settle();
+    if (__builtin_expect(wave_nan(nan_sum(acc)), 0)) {  // again, as in the forward
+        uint16_t* buf = wave < 2 ? KV0[wave] : KV1[wave - 2];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int t = 0; t < nkv; ++t) {
+            f32x4 s[4], ds[4];
+            stage_alone<D>(lane, K + hoff, buf, t * kTile, N);
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) s[kb] = block_dot<D>(buf, 16 * kb, qf, c16, g);
+            stage_alone<D>(lane, V + hoff, buf, t * kTile, N);
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                const f32x4 dp = block_dot<D>(buf, 16 * kb, uf, c16, g);
+                if (t < nplain) grads(plain, t, kb, s[kb], dp, ds[kb]);
+                else grads(masked, t, kb, s[kb], dp, ds[kb]);
+            }
+            stage_alone<D>(lane, K + hoff, buf, t * kTile, N);
+            tr_accumulate<D, true>(buf, ds, acc, c16, g);
+            mfma_settle();
+        }
     }
 
     if (qok) {
@@ -459,6 +493,11 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
     const float* tsh = TS + (size_t)bh * T * kF32Stat;
 
     f32x4 accV[MB], accK[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        accV[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        accK[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     const int qt0 = causal ? tile : 0;  // the diagonal tile first, masked
 
     TileDma<D> dma;
@@ -475,73 +514,88 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void f32_dkdv_kernel(
                      lds_addr(ST + wave * kTile), (uint32_t)lane * 4u);
     };
     wait_vm_lgkm0<0>();
-    auto walk = [&](auto exact_inf) {
+    fill(qt0 < T ? qt0 : 0, QU0, ST0);
+    wait_vm_lgkm0<0>();
+    __syncthreads();
+
+    // P and dS of query block qb of tile qt from its S and dP and the tile's statistics
+    auto grads = [&](auto masked, int qt, int qb, const float* st, const f32x4& s, const f32x4& dp,
+                     f32x4& p, f32x4& ds) {
+        constexpr bool MASK = decltype(masked)::value;
+        const f32x4 mq = *reinterpret_cast<const f32x4*>(st + 16 * qb + 4 * g);
+        const f32x4 lq = *reinterpret_cast<const f32x4*>(st + kTile + 16 * qb + 4 * g);
+        const f32x4 dq = *reinterpret_cast<const f32x4*>(st + 2 * kTile + 16 * qb + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float pv = fexp2((scale * s[i] - mq[i]) * lg) * lq[i];
+            if constexpr (MASK) {
+                const int query = qt * kTile + 16 * qb + 4 * g + i;
+                pv = (!causal || krow <= query) ? pv : 0.f;
+            }
+            p[i] = pv;
+            ds[i] = pv * (dp[i] - dq[i]);
+            if constexpr (MASK) ds[i] = pv != 0.f ? ds[i] : 0.f;
+        }
+    };
+    auto step = [&](auto masked, int qt, uint16_t (*QUc)[kTile * D], const float* st,
+                    uint16_t (*QUn)[kTile * D], float* STn) {
+        const uint16_t* Qc = QUc[0];
+        const uint16_t* Uc = QUc[1];
+        if (qt + 1 < T) fill(qt + 1, QUn, STn);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 p[4], ds[4];
+#pragma unroll
+        for (int qb = 0; qb < 4; ++qb) {
+            const f32x4 s = block_dot<D>(Qc, 16 * qb, kf, c16, g);
+            const f32x4 dp = block_dot<D>(Uc, 16 * qb, vf, c16, g);
+            grads(masked, qt, qb, st, s, dp, p[qb], ds[qb]);
+        }
+        tr_accumulate<D, false>(Uc, p, accV, c16, g);
+        tr_accumulate<D, false>(Qc, ds, accK, c16, g);
+        wait_vm_lgkm0<0>();
+        __syncthreads();
+    };
+    const std::false_type plain;
+    const std::true_type masked;
+    int qt = qt0;
+    // The first tile (there always is one) is staged in slot 0 whatever its index:
+    // slots alternate with the step count from qt0.
+    if (causal) step(masked, qt, QU0, ST0, QU1, ST1);
+    else step(plain, qt, QU0, ST0, QU1, ST1);
+    ++qt;
+    // two steps a turn, as in the passes above
+    for (; qt + 1 < T; qt += 2) {
+        step(plain, qt, QU1, ST1, QU0, ST0);
+        step(plain, qt + 1, QU0, ST0, QU1, ST1);
+    }
+    if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
+    mfma_settle();
+    if (__builtin_expect(wave_nan(nan_sum(accV) + nan_sum(accK)), 0)) {  // again, as in the forward
+        uint16_t* buf = wave < 2 ? QU0[wave] : QU1[wave - 2];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             accV[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
             accK[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        fill(qt0 < T ? qt0 : 0, QU0, ST0);
-        wait_vm_lgkm0<0>();
-        __syncthreads();
-
-        auto step = [&](auto masked, int qt, uint16_t (*QUc)[kTile * D], const float* st,
-                        uint16_t (*QUn)[kTile * D], float* STn) {
-            constexpr bool MASK = decltype(masked)::value;
-            const uint16_t* Qc = QUc[0];
-            const uint16_t* Uc = QUc[1];
-            if (qt + 1 < T) fill(qt + 1, QUn, STn);
-            __builtin_amdgcn_sched_barrier(0);
-            f32x4 p[4], ds[4];
+#pragma unroll 1
+        for (int t = qt0; t < T; ++t) {
+            f32x4 s[4], p[4], ds[4];
+            stage_alone<D>(lane, Q + hoff, buf, t * kTile, N);
+#pragma unroll
+            for (int qb = 0; qb < 4; ++qb) s[qb] = block_dot<D>(buf, 16 * qb, kf, c16, g);
+            stage_alone<D>(lane, dO + hoff, buf, t * kTile, N);
+            const float* st = tsh + (size_t)t * kF32Stat;
 #pragma unroll
             for (int qb = 0; qb < 4; ++qb) {
-                const f32x4 mq = *reinterpret_cast<const f32x4*>(st + 16 * qb + 4 * g);
-                const f32x4 lq = *reinterpret_cast<const f32x4*>(st + kTile + 16 * qb + 4 * g);
-                const f32x4 dq = *reinterpret_cast<const f32x4*>(st + 2 * kTile + 16 * qb + 4 * g);
-                const f32x4 s = block_dot<D>(Qc, 16 * qb, kf, c16, g);
-                const f32x4 dp = block_dot<D>(Uc, 16 * qb, vf, c16, g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float pv = fexp2((scale * s[i] - mq[i]) * lg) * lq[i];
-                    if constexpr (MASK) {
-                        const int query = qt * kTile + 16 * qb + 4 * g + i;
-                        pv = (!causal || krow <= query) ? pv : 0.f;
-                    }
-                    p[qb][i] = pv;
-                    ds[qb][i] = pv * (dp[i] - dq[i]);
-                    if constexpr (MASK) ds[qb][i] = pv != 0.f ? ds[qb][i] : 0.f;
-                }
+                const f32x4 dp = block_dot<D>(buf, 16 * qb, vf, c16, g);
+                if (t == qt0) grads(masked, t, qb, st, s[qb], dp, p[qb], ds[qb]);
+                else grads(plain, t, qb, st, s[qb], dp, p[qb], ds[qb]);
             }
-            tr_accumulate<D, decltype(exact_inf)::value>(Uc, p, accV, c16, g);
-            tr_accumulate<D, decltype(exact_inf)::value>(Qc, ds, accK, c16, g);
-            if constexpr (decltype(exact_inf)::value) mfma_settle();
-            wait_vm_lgkm0<0>();
-            __syncthreads();
-        };
-        const std::false_type plain;
-        const std::true_type masked;
-        int qt = qt0;
-        // The first tile is staged in slot 0 whatever its index: slots alternate
-        // with the step count from qt0.
-        if (causal && qt < T) {
-            step(masked, qt, QU0, ST0, QU1, ST1);
-            ++qt;
-        } else if (qt < T) {
-            step(plain, qt, QU0, ST0, QU1, ST1);
-            ++qt;
+            tr_accumulate<D, true>(buf, p, accV, c16, g);
+            stage_alone<D>(lane, Q + hoff, buf, t * kTile, N);
+            tr_accumulate<D, true>(buf, ds, accK, c16, g);
+            mfma_settle();
         }
-        // two steps a turn, as in the passes above
-        for (; qt + 1 < T; qt += 2) {
-            step(plain, qt, QU1, ST1, QU0, ST0);
-            step(plain, qt + 1, QU0, ST0, QU1, ST1);
-        }
-        if (qt < T) step(plain, qt, QU1, ST1, QU0, ST0);
-    };
-    walk(std::false_type{});
-    mfma_settle();
-    if (workgroup_nan(nan_sum(accV) + nan_sum(accK), QU0, wave)) {
-        __syncthreads();
-        walk(std::true_type{});
     }
 
     if (krow < N) {
