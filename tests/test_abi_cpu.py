@@ -204,13 +204,15 @@ def _few(nq, nk, G):
 def test_few_query_forward_workspace_and_validation(lib):
     """The workspace that the forward with split keys asks for, and its host-side
     checks."""
+    import paper_2609_34272_amd as gpa
     f = lib.gpa_attn_fwd_varlen_workspace_bytes
     few = (8, 32, 30000, 16, 4, 4, 5115, 128)  # 8 sequences of 4 queries
     n = f(*few)
     rows = 4 * (30000 // 4 + 4 * 32 + 17 * 8)
     assert n == rows * 128 * 4 + -(-rows * 8 // 256) * 256
-    # no key run is long enough to be split
-    assert f(8, 32, 4000, 16, 4, 4, 511, 128) == 0 and f(8, 32, 4000, 16, 4, 4, 512, 128) > 0
+    # no key run is long enough to be split: the line that the binding knows
+    least = gpa._SPLIT_MIN_KEYS
+    assert f(8, 32, 4000, 16, 4, 4, least - 1, 128) == 0 and f(8, 32, 4000, 16, 4, 4, least, 128) > 0
     # whether there are few queries is a matter of each sequence, not of the longest
     assert f(8, 1032, 30000, 16, 4, 129, 5115, 128) > 0
     # invalid shapes
